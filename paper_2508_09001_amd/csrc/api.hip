@@ -305,10 +305,11 @@ retro_status retro_decode_attend(const retro_dims* dims, int32_t step, const voi
   hipStream_t s = (hipStream_t)stream;
   float* o_ws = ws_at(workspace, g.ws_opart);
   float* l_ws = ws_at(workspace, g.ws_lpart);
-  hipError_t e = retro::launch_attend(g, step, q_window, *cache, *sel, nullptr, o_ws, l_ws,
+  const Geometry ga = retro::attend_geometry(g);
+  hipError_t e = retro::launch_attend(ga, step, q_window, *cache, *sel, nullptr, o_ws, l_ws,
                                       (char*)workspace + g.ws_dummy, s);
   if (e == hipSuccess)
-    e = retro::launch_combine_merge(g, step, 0, o_ws, l_ws, sel->num_selected, nullptr, nullptr,
+    e = retro::launch_combine_merge(ga, step, 0, o_ws, l_ws, sel->num_selected, nullptr, nullptr,
                                     o_part, lse_part, nullptr, nullptr, nullptr, nullptr, s);
   return from_hip(e);
 }
@@ -322,8 +323,8 @@ retro_status retro_decode_attend_partials(const retro_dims* dims, int32_t step,
   if (st != RETRO_OK) return st;
   if (!q_window || !cache_ok(cache) || !sel_ok(sel)) return RETRO_EINVAL;
   if ((st = check_ws(g, workspace, ws_bytes)) != RETRO_OK) return st;
-  return from_hip(retro::launch_attend(g, step, q_window, *cache, *sel, nullptr,
-                                       ws_at(workspace, g.ws_opart), ws_at(workspace, g.ws_lpart),
+  return from_hip(retro::launch_attend(retro::attend_geometry(g), step, q_window, *cache, *sel,
+                                       nullptr, ws_at(workspace, g.ws_opart), ws_at(workspace, g.ws_lpart),
                                        (char*)workspace + g.ws_dummy, (hipStream_t)stream));
 }
 
@@ -337,7 +338,6 @@ retro_status retro_step_attend_partials(const retro_dims* dims, int32_t step,
   if (!q_window || !cache_ok(cache) || !sel_ok(sel)) return RETRO_EINVAL;
   if ((st = check_ws(g, workspace, ws_bytes)) != RETRO_OK) return st;
   if (!retro::attend_selects(g)) return RETRO_EUNSUPPORTED;
-  int32_t* phys = reinterpret_cast<int32_t*>((char*)workspace + g.ws_phys);
   int32_t* tok = reinterpret_cast<int32_t*>((char*)workspace + g.ws_tok);
   if (one_launch(g)) {
     int32_t* err = reinterpret_cast<int32_t*>((char*)workspace + g.ws_err);
@@ -347,27 +347,12 @@ retro_status retro_step_attend_partials(const retro_dims* dims, int32_t step,
                                               wait_limit(g), wait_bias(g), nullptr, nullptr,
                                               nullptr, (hipStream_t)stream));
   }
-  return from_hip(retro::launch_attend_select(g, step, q_window, *cache, *sel, phys,
-                                              ws_at(workspace, g.ws_scores),
+  return from_hip(retro::launch_attend_select(retro::attend_geometry(g), step, q_window, *cache,
+                                              *sel, ws_at(workspace, g.ws_scores),
                                               ws_at(workspace, g.ws_opart),
                                               ws_at(workspace, g.ws_lpart), tok,
                                               (char*)workspace + g.ws_dummy, (hipStream_t)stream));
 }
-
-namespace {
-// Attention workgroups per KV head from which the selection runs once per head
-// at the end of the score launch instead of in front of every attention
-// workgroup, which repeats it once per workgroup.  Measured per layer-step:
-// 64 per head (131K-token tables, W = 64: 32 splits x 2 row groups) 50.2 us
-// in the score launch vs 52.4 in the attention launch; 16 per head (the
-// long-generation workload) 115.2 vs 111.4; 2 per head (batch 16) 77.4 vs 63.8.
-constexpr int kSelectInScoresFrom = 64;
-
-bool select_in_attention(const Geometry& gp) {
-  if (!retro::attend_selects(gp) || (gp.flags & RETRO_FLAG_SELECT_IN_SCORES)) return false;
-  return !(retro::score_selects(gp) && gp.n_splits * gp.n_rgroups >= kSelectInScoresFrom);
-}
-}  // namespace
 
 retro_status retro_step_launches(const retro_dims* dims, int32_t* launches) {
   Geometry g;
@@ -378,8 +363,6 @@ retro_status retro_step_launches(const retro_dims* dims, int32_t* launches) {
   gp.token_pending = 1;
   if (one_launch(gp)) {
     *launches = 1;
-  } else if (select_in_attention(gp)) {
-    *launches = 3;
   } else {
     *launches = retro::score_selects(gp) ? 3 : 4;
   }
@@ -440,12 +423,13 @@ retro_status retro_step(const retro_dims* dims, int32_t step, const void* q_wind
   if (retro::reuse_step(g, step)) {
     // top-k reuse: the token's append (with Alg. 2's current-page rule and the
     // seq_lens advance), Alg. 2 on the kept selection, attention, combine + merge
+    const Geometry ga = retro::attend_geometry(g);
     hipError_t e = retro::launch_append(g, step, *cache, k_new, v_new, s);
     if (e == hipSuccess) e = retro::launch_reuse_mask(g, step, *cache, *sel, s);
     if (e == hipSuccess)
-      e = retro::launch_attend(g, step, q_window, *cache, *sel, nullptr, o_ws, l_ws, dummy, s);
+      e = retro::launch_attend(ga, step, q_window, *cache, *sel, nullptr, o_ws, l_ws, dummy, s);
     if (e == hipSuccess)
-      e = retro::launch_combine_merge(g, step, 2, o_ws, l_ws, sel->num_selected, nullptr,
+      e = retro::launch_combine_merge(ga, step, 2, o_ws, l_ws, sel->num_selected, nullptr,
                                       nullptr, nullptr, nullptr, ocache, o_out, lse_out, cache, s);
     return from_hip(e);
   }
@@ -460,16 +444,17 @@ retro_status retro_step(const retro_dims* dims, int32_t step, const void* q_wind
                                               workspace, o_ws, l_ws, tok, err, wait_limit(g),
                                               wait_bias(g), ocache, o_out, lse_out, s));
   }
-  if (select_in_attention(gp)) {
+  const Geometry ga = retro::attend_geometry(gp);
+  if (retro::attend_selects(gp) && !(gp.flags & RETRO_FLAG_SELECT_IN_SCORES)) {
     // score (+ the token's append) -> attention with the selection in front ->
     // combine + merge (+ last_loaded update, + seq_lens advance)
     hipError_t e = retro::launch_score(gp, step, q_cur, qbs, *cache, k_new, v_new, scores,
                                        nullptr, nullptr, nullptr, s);
     if (e == hipSuccess)
-      e = retro::launch_attend_select(gp, step, q_window, *cache, *sel, phys, scores, o_ws, l_ws,
-                                      tok, dummy, s);
+      e = retro::launch_attend_select(ga, step, q_window, *cache, *sel, scores, o_ws, l_ws, tok,
+                                      dummy, s);
     if (e == hipSuccess)
-      e = retro::launch_combine_merge(gp, step, 2, o_ws, l_ws, sel->num_selected, nullptr,
+      e = retro::launch_combine_merge(ga, step, 2, o_ws, l_ws, sel->num_selected, nullptr,
                                       nullptr, nullptr, nullptr, ocache, o_out, lse_out, cache, s,
                                       sel->selected, tok);
     return from_hip(e);
@@ -482,9 +467,9 @@ retro_status retro_step(const retro_dims* dims, int32_t step, const void* q_wind
   if (e == hipSuccess && !retro::score_selects(gp))
     e = retro::launch_topk_mask(gp, step, scores, *cache, *sel, phys, s);
   if (e == hipSuccess)
-    e = retro::launch_attend(gp, step, q_window, *cache, *sel, phys, o_ws, l_ws, dummy, s);
+    e = retro::launch_attend(ga, step, q_window, *cache, *sel, phys, o_ws, l_ws, dummy, s);
   if (e == hipSuccess)
-    e = retro::launch_combine_merge(gp, step, 2, o_ws, l_ws, sel->num_selected, nullptr, nullptr,
+    e = retro::launch_combine_merge(ga, step, 2, o_ws, l_ws, sel->num_selected, nullptr, nullptr,
                                     nullptr, nullptr, ocache, o_out, lse_out, cache, s);
   return from_hip(e);
 }

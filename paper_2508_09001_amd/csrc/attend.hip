@@ -30,7 +30,7 @@
 //
 // Output: per split and row, the normalised partial output and its natural-log
 // normaliser, combined across splits by the merge kernel.
-#include "roles.h"
+#include "threshold.h"
 
 namespace retro {
 namespace {
@@ -78,83 +78,27 @@ hipError_t attend_d(const AttendArgs& a, hipStream_t s) {
   return a.g.rtw == 1 ? attend_t<T, D, 1>(a, s) : attend_t<T, D, 2>(a, s);
 }
 
-// The selection of KV head bh as every attention workgroup of the head runs it
-// (topk_core over the head's scores, the same result in each): slots [first,
-// first + pages_per_split) of the kept pages go to l_lp / l_m / l_ph (logical
-// page, mask value, physical page) and the count to *s_k; the `writer`
-// workgroup also writes the selection rows (-1 past the count), the count, and
-// tok_out[bh] = the step token's page if it is not kept, else -1.  Ends with a
-// barrier.  len_of / tok_lp / wait as for topk_core.
-template <int PER, typename LenOf, typename Wait>
-__device__ __forceinline__ void select_for_split(const TopkArgs& ta, int bh, int first, bool writer,
-                                                 LenOf&& len_of, const int& tok_lp,
-                                                 Wait&& wait, char* lds,
-                                                 int (&l_lp)[kMaxSplitPages],
-                                                 int (&l_m)[kMaxSplitPages],
-                                                 int (&l_ph)[kMaxSplitPages], int& s_k,
-                                                 int32_t* tok_out) {
-  const Geometry& g = ta.g;
-  const int tid = thread_index();
-  uint32_t* hist = reinterpret_cast<uint32_t*>(lds);
-  int* small = reinterpret_cast<int*>(hist + kTopkHistWords);
-  int32_t* sel_row = ta.selected + (int64_t)bh * g.k_max;
-  int32_t* m_row = ta.mask + (int64_t)bh * g.k_max;
-  int32_t* ph_row = ta.sel_phys + (int64_t)bh * g.k_max;
-  const int k = topk_core<PER, kAttendThreads / 64>(
-      ta, bh, len_of, tok_lp, hist, small, wait, [&](int pos, int p, int a_old, int phys) {
-        const int ph = (phys >= 0 && phys < g.num_phys) ? phys : -1;
-        if (pos >= first && pos < first + g.pages_per_split) {
-          l_lp[pos - first] = p;
-          l_m[pos - first] = a_old;
-          l_ph[pos - first] = ph;
-        }
-        if (writer) {
-          if (pos >= 0) {
-            sel_row[pos] = p;
-            m_row[pos] = a_old;
-            ph_row[pos] = ph;
-          }
-          if (p == tok_lp) tok_out[bh] = pos < 0 ? p : -1;
-        }
-      });
-  if (writer) {
-    for (int i = k + tid; i < g.k_max; i += kAttendThreads) {
-      sel_row[i] = -1;
-      m_row[i] = -1;
-      ph_row[i] = -1;
-    }
-    if (tid == 0) {
-      ta.num_selected[bh] = k;
-      if (tok_lp < 0) tok_out[bh] = -1;
-    }
-  }
-  if (tid == 0) s_k = k;
-  __syncthreads();  // the split's page list and the count are in LDS
-}
-
-// Attention with the page selection in front: every workgroup of a KV head
-// runs the head's top-k (the same computation on the same scores, so the same
-// result) and takes its split's slots of the selection from LDS, instead of
-// waiting for a selection launch and reading the rows back.  The workgroup of
-// split 0, row group 0 writes the selection rows, the count and, for the
-// step's token page, -1 when it is kept and its logical page otherwise
-// (tok_out[bh]); last_loaded is left alone here (other workgroups of the head
-// read it) and updated by the combine launch from those outputs.  The
+// Attention with the page selection in front: every workgroup of a KV head makes
+// the head's selection (the same computation on the same scores, so the same
+// result) and takes its split's slots of it from LDS, instead of waiting for
+// a selection launch and reading the rows back.  The workgroup of the last
+// split, row group 0 writes the selection rows, the count and the token's page
+// (TopkArgs::tok_out); last_loaded is left alone here (other workgroups of the
+// head read it) and updated by the combine launch from those outputs.  The
 // selection's histograms share LDS with the chunk staging, which is only used
 // after the page list is in place.
 template <typename T, int D, int RTW, int PER>
-__global__ void __launch_bounds__(kAttendThreads) attend_select_kernel(AttendArgs a, TopkArgs ta,
-                                                                       int32_t* tok_out) {
+__global__ void __launch_bounds__(kAttendThreads) attend_select_kernel(AttendArgs a, TopkArgs ta) {
   using TL = Tiles<T, D>;
   constexpr int MAXP = (TL::PIECES + kAttendThreads - 1) / kAttendThreads;
   constexpr int kStageBytes = 2 * TL::BUF_ELEMS * (int)sizeof(T);
-  constexpr int kSelectBytes = (kTopkHistWords + kTopkSmall) * 4;
-  __shared__ __attribute__((aligned(16))) char lds[std::max(kStageBytes, kSelectBytes)];
+  using Thr = ThrLds<PER, kAttendThreads / 64>;
+  __shared__ __attribute__((aligned(16))) char lds[std::max(kStageBytes, (int)sizeof(Thr))];
   __shared__ int s_phys[kMaxSplitPages];
   __shared__ int s_page[kMaxSplitPages];
   __shared__ int s_mask[kMaxSplitPages];
   __shared__ int l_lp[kMaxSplitPages], l_m[kMaxSplitPages], l_ph[kMaxSplitPages];
-  __shared__ int s_k, s_tok;
+  __shared__ int s_tok;
   const Geometry& g = a.g;
   int u = xcd_remap(blockIdx.x, gridDim.x);
   const int split = u % g.n_splits;
@@ -162,59 +106,51 @@ __global__ void __launch_bounds__(kAttendThreads) attend_select_kernel(AttendArg
   const int rg = u % g.n_rgroups;
   u /= g.n_rgroups;
   const int h = u % g.hk, b = u / g.hk;
-  const int bh = b * g.hk + h;
-  const bool writer = split == 0 && rg == 0;
+  const bool writer = split == g.n_splits - 1 && rg == 0;
   const int first = split * g.pages_per_split;
-  int seq_len = 0, tok_lp = -1;
+  int seq_len = 0, k = 0;
   auto select = [&] {
-    select_for_split<PER>(
-        ta, bh, first, writer,
-        [&] {
-          const int pos = a.seq_lens[b];
-          seq_len = pos;
-          tok_lp = -1;
-          if (g.token_pending && token_phys(g, a.pt, b, pos) >= 0) {
-            seq_len = pos + 1;
-            tok_lp = pos / g.P;
-          }
-          return seq_len;
-        },
-        tok_lp, [] {}, lds, l_lp, l_m, l_ph, s_k, tok_out);
+    int tok_lp = -1;
+    seq_len = a.seq_lens[b];
+    if (g.token_pending && token_phys(g, a.pt, b, seq_len) >= 0) {
+      tok_lp = seq_len / g.P;
+      seq_len += 1;
+    }
+    k = select_role(ta, b * g.hk + h, seq_len, tok_lp, *reinterpret_cast<Thr*>(lds), writer,
+                    [&](int q, int p, int m, int ph) {
+                      if (q >= first && q < first + g.pages_per_split) {
+                        l_lp[q - first] = p;
+                        l_m[q - first] = m;
+                        l_ph[q - first] = ph;
+                      }
+                    });
+    __syncthreads();  // the split's page list is in LDS
   };
   attend_role<T, D, RTW, MAXP, RTW == 1, false>(
       a, b, h, rg, split, [&] { return seq_len; }, reinterpret_cast<T*>(lds), s_phys, s_page,
-      s_mask, &s_tok, -1, select, [&](int t, int, int& lp, int& m, int& phys) {
-        if (t < g.pages_per_split) {
+      s_mask, &s_tok, -1, select, [&](int t, int& lp, int& m, int& phys) {
+        if (t < min(g.pages_per_split, k - first)) {
           lp = l_lp[t];
           m = l_m[t];
           phys = l_ph[t];
         }
-        return s_k;
+        return k;
       });
 }
 
-template <typename T, int D, int PER>
-hipError_t attend_select_p(const AttendArgs& a, const TopkArgs& ta, int32_t* tok_out,
-                           hipStream_t s) {
+template <typename T, int D>
+hipError_t attend_select_d(const AttendArgs& a, const TopkArgs& ta, hipStream_t s) {
   const Geometry& g = a.g;
   const int64_t n = (int64_t)g.n_splits * g.n_rgroups * g.hk * g.batch;
-  if (64 * g.waves != kAttendThreads || g.max_pages > PER * kAttendThreads) return hipErrorInvalidValue;
-  if (g.rtw == 1)
-    attend_select_kernel<T, D, 1, PER><<<(unsigned)n, kAttendThreads, 0, s>>>(a, ta, tok_out);
-  else
-    attend_select_kernel<T, D, 2, PER><<<(unsigned)n, kAttendThreads, 0, s>>>(a, ta, tok_out);
-  return hipGetLastError();
-}
-
-template <typename T, int D>
-hipError_t attend_select_d(const AttendArgs& a, const TopkArgs& ta, int32_t* tok_out,
-                           hipStream_t s) {
-  const int mp = a.g.max_pages;
-  if (mp <= 2 * kAttendThreads) return attend_select_p<T, D, 2>(a, ta, tok_out, s);
-  if (mp <= 5 * kAttendThreads) return attend_select_p<T, D, 5>(a, ta, tok_out, s);
-  if (mp <= 6 * kAttendThreads) return attend_select_p<T, D, 6>(a, ta, tok_out, s);
-  if (mp <= 9 * kAttendThreads) return attend_select_p<T, D, 9>(a, ta, tok_out, s);
-  return attend_select_p<T, D, 12>(a, ta, tok_out, s);
+  if (64 * g.waves != kAttendThreads) return hipErrorInvalidValue;
+  return with_select_per(g.max_pages, [&](auto per) {
+    constexpr int PER = decltype(per)::value;
+    if (g.rtw == 1)
+      attend_select_kernel<T, D, 1, PER><<<(unsigned)n, kAttendThreads, 0, s>>>(a, ta);
+    else
+      attend_select_kernel<T, D, 2, PER><<<(unsigned)n, kAttendThreads, 0, s>>>(a, ta);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace
@@ -255,25 +191,23 @@ hipError_t launch_attend(const Geometry& g, int step, const void* q_window,
                          hipStream_t s) {
   if (!dummy) return hipErrorInvalidValue;
   const AttendArgs a = make_attend_args(g, step, q_window, c, sel, sel_phys, o_ws, l_ws, dummy);
-  if (g.dtype == RETRO_BF16) return g.D == 128 ? attend_d<bf16_t, 128>(a, s) : attend_d<bf16_t, 64>(a, s);
+  if (g.dtype == RETRO_BF16) return launch_stream_attend(a, nullptr, s);
   return g.D == 128 ? attend_d<float, 128>(a, s) : attend_d<float, 64>(a, s);
 }
 
-bool attend_selects(const Geometry& g) { return g.max_pages <= 12 * kAttendThreads; }
+bool attend_selects(const Geometry& g) { return g.max_pages <= kSelectPer * kAttendThreads; }
 
 hipError_t launch_attend_select(const Geometry& g, int step, const void* q_window,
                                 const retro_kv_cache& c, const retro_selection& sel,
-                                int32_t* sel_phys, const float* scores, float* o_ws, float* l_ws,
-                                int32_t* tok_out, const void* dummy, hipStream_t s) {
-  if (!attend_selects(g) || !sel_phys || !tok_out || !dummy) return hipErrorInvalidValue;
-  const AttendArgs a = make_attend_args(g, step, q_window, c, sel, sel_phys, o_ws, l_ws, dummy);
+                                const float* scores, float* o_ws, float* l_ws, int32_t* tok_out,
+                                const void* dummy, hipStream_t s) {
+  if (!attend_selects(g) || !tok_out || !dummy) return hipErrorInvalidValue;
+  AttendArgs a = make_attend_args(g, step, q_window, c, sel, nullptr, o_ws, l_ws, dummy);
+  a.sel_phys = tok_out;  // non-null: the page list carries physical pages (never read here)
   const TopkArgs ta{g, step, scores, c.page_table, c.last_loaded, sel.selected, sel.mask,
-                    sel.num_selected, sel_phys};
-  if (g.dtype == RETRO_BF16)
-    return g.D == 128 ? attend_select_d<bf16_t, 128>(a, ta, tok_out, s)
-                      : attend_select_d<bf16_t, 64>(a, ta, tok_out, s);
-  return g.D == 128 ? attend_select_d<float, 128>(a, ta, tok_out, s)
-                    : attend_select_d<float, 64>(a, ta, tok_out, s);
+                    sel.num_selected, nullptr, 0, tok_out};
+  if (g.dtype == RETRO_BF16) return launch_stream_attend(a, &ta, s);
+  return g.D == 128 ? attend_select_d<float, 128>(a, ta, s) : attend_select_d<float, 64>(a, ta, s);
 }
 
 }  // namespace retro

@@ -112,16 +112,20 @@ hipError_t launch_attend(const Geometry& g, int step, const void* q_window,
                          const retro_kv_cache& c, const retro_selection& sel,
                          const int32_t* sel_phys, float* o_ws, float* l_ws, const void* dummy,
                          hipStream_t s);
-// Attention with the page selection (top-k + Alg. 2's mask) computed by each
-// of its workgroups (attend_selects(g)); writes the selection outputs (rows,
-// mask, physical pages, count) but not last_loaded: the combine launch after
-// it takes `selected` = sel.selected and `tok_out` to update it.  scores: the
-// score launch's page scores; tok_out: [batch * h_k] ints of workspace.
+// The attention of the multi-launch plans for bf16 layers (stream_attend.hip) has
+// a split of its own: attend_geometry(g) is g with that split (g itself for
+// fp32), to be used for launch_attend and the combine of its partials.
+Geometry attend_geometry(const Geometry& g);
+// Attention with the page selection (top-k + Alg. 2's mask) made by each of its
+// workgroups from the score launch's page scores (attend_selects(g); g from
+// attend_geometry); writes the selection outputs (rows, mask, count) but not
+// last_loaded: the combine launch after it takes `selected` = sel.selected and
+// `tok_out` ([batch * h_k] ints of workspace) to update it.
 bool attend_selects(const Geometry& g);
 hipError_t launch_attend_select(const Geometry& g, int step, const void* q_window,
                                 const retro_kv_cache& c, const retro_selection& sel,
-                                int32_t* sel_phys, const float* scores, float* o_ws, float* l_ws,
-                                int32_t* tok_out, const void* dummy, hipStream_t s);
+                                const float* scores, float* o_ws, float* l_ws, int32_t* tok_out,
+                                const void* dummy, hipStream_t s);
 // Page scores (+ the token's append), selection, attention and (with o_out)
 // the combine + merge of a step in one launch (step_attend.hip): the
 // workgroups of a KV head score its pages, publish them as tagged words, each
@@ -150,15 +154,13 @@ int compute_units();
 // With g.token_pending and a cache, the launch also advances seq_lens past the
 // step's token (when its page is mapped).  With `selected` and `tok_upd` (from
 // launch_attend_select; num_selected and cache required), it also applies the
-// step's last_loaded update.  With `err` (mode 2), rows are written as NaN if
-// that word is set (a bounded wait of the launch before ran out).
+// step's last_loaded update.
 hipError_t launch_combine_merge(const Geometry& g, int step, int mode, const float* o_ws,
                                 const float* l_ws, const int32_t* num_selected,
                                 const float* o_part, const float* l_part, float* o_part_out,
                                 float* l_part_out, const retro_output_cache* oc, float* o_out,
                                 float* lse_out, const retro_kv_cache* cache, hipStream_t s,
                                 const int32_t* selected = nullptr,
-                                const int32_t* tok_upd = nullptr,
-                                const int32_t* err = nullptr);
+                                const int32_t* tok_upd = nullptr);
 
 }  // namespace retro

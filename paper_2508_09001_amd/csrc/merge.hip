@@ -21,18 +21,25 @@ namespace {
 
 constexpr int kWaves = 2;  // wavefronts (work units) per workgroup: 256 workgroups at the headline shape, one per CU
 
-__device__ __forceinline__ void update_last_loaded(const MergeArgs& a, int bh) {
+// Alg. 2's update for kUpdPages slots of KV head bh's selection row, by one
+// wavefront: all of its row entries are requested at once.
+constexpr int kUpdPages = 256;
+__device__ __forceinline__ void update_last_loaded(const MergeArgs& a, int bh, int part) {
   const Geometry& g = a.g;
   const int lane = threadIdx.x & 63;
-  const int k = a.nsel[bh];
+  const int k = min(a.nsel[bh], g.k_max);
   const int tok = a.tok_upd[bh];
   const int32_t* srow = a.sel_upd + (int64_t)bh * g.k_max;
   int32_t* arow = a.a_upd + (int64_t)bh * g.max_pages;
-  for (int i = lane; i < k && i < g.k_max; i += 64) {
-    const int p = srow[i];
-    if (p >= 0 && p < g.max_pages) arow[p] = a.step;
-  }
-  if (lane == 0 && tok >= 0 && tok < g.max_pages) arow[tok] = a.step - 1;
+  int p[kUpdPages / 64];
+#pragma unroll
+  for (int j = 0; j < kUpdPages / 64; ++j)
+    p[j] = srow[min(part * kUpdPages + j * 64 + lane, g.k_max - 1)];
+#pragma unroll
+  for (int j = 0; j < kUpdPages / 64; ++j)
+    if (part * kUpdPages + j * 64 + lane < k && p[j] >= 0 && p[j] < g.max_pages)
+      arow[p[j]] = a.step;
+  if (part == 0 && lane == 0 && tok >= 0 && tok < g.max_pages) arow[tok] = a.step - 1;
 }
 
 // GS: splits whose rows are loaded and folded in together, the smallest power
@@ -44,26 +51,18 @@ __global__ void __launch_bounds__(64 * kWaves) combine_merge_kernel(MergeArgs a)
   const Geometry& g = a.g;
   const int nunits = g.batch * g.hq * a.xs;
   const int mblocks = (nunits + kWaves - 1) / kWaves;
-  // A bounded wait of the launch that produced the partials ran out (or it
-  // refused a workspace of another geometry): the partials and the selection
-  // are not to be trusted, so the outputs are NaN and the caller's state (the
-  // output cache, last_loaded, seq_lens) is left as it was.
-  const bool failed = a.err && *a.err != 0;
   if ((int)blockIdx.x >= mblocks) {
-    // workgroups past the merge units: Alg. 2's last_loaded update, one KV
-    // head per wavefront
-    const int bh = ((int)blockIdx.x - mblocks) * kWaves + (threadIdx.x >> 6);
-    if (bh < g.batch * g.hk && !failed) update_last_loaded(a, bh);
+    // workgroups past the merge units: Alg. 2's last_loaded update, kUpdPages
+    // slots of a KV head per wavefront
+    const int parts = (g.k_max + kUpdPages - 1) / kUpdPages;
+    const int i = ((int)blockIdx.x - mblocks) * kWaves + (threadIdx.x >> 6);
+    if (i < g.batch * g.hk * parts) update_last_loaded(a, i / parts, i % parts);
     return;
   }
   // the wavefront index as a uniform value: the unit's indices and row offsets
   // then stay in scalar registers
   const int u = xcd_remap(blockIdx.x, mblocks) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (u >= nunits) return;  // uniform per wavefront; no barrier follows
-  if (failed) {
-    poison_unit<D>(a, unit_pos(a, u));
-    return;
-  }
   merge_unit<D, GS>(a, unit_pos(a, u));
   if (blockIdx.x == 0 && threadIdx.x < 64 && g.token_pending && a.seq_lens) {
     // after the unit's own loads (the two lookups here are dependent): the
@@ -103,7 +102,6 @@ MergeArgs make_merge_args(const Geometry& g, int step, int mode, const float* o_
   a.a_upd = nullptr;
   a.sel_upd = nullptr;
   a.tok_upd = nullptr;
-  a.err = nullptr;
   return a;
 }
 
@@ -112,22 +110,21 @@ hipError_t launch_combine_merge(const Geometry& g, int step, int mode, const flo
                                 const float* o_part, const float* l_part, float* o_part_out,
                                 float* l_part_out, const retro_output_cache* oc, float* o_out,
                                 float* lse_out, const retro_kv_cache* cache, hipStream_t s,
-                                const int32_t* selected, const int32_t* tok_upd,
-                                const int32_t* err) {
+                                const int32_t* selected, const int32_t* tok_upd) {
   MergeArgs a = make_merge_args(g, step, mode, o_ws, l_ws, num_selected, o_part, l_part,
                                 o_part_out, l_part_out, oc, o_out, lse_out);
   if (cache) {
     a.seq_lens = cache->seq_lens;
     a.pt = cache->page_table;
   }
-  a.err = err;
   int64_t upd_blocks = 0;
   if (selected && tok_upd) {
     if (!cache || !num_selected) return hipErrorInvalidValue;
     a.a_upd = cache->last_loaded;
     a.sel_upd = selected;
     a.tok_upd = tok_upd;
-    upd_blocks = ((int64_t)g.batch * g.hk + kWaves - 1) / kWaves;
+    const int64_t parts = (g.k_max + kUpdPages - 1) / kUpdPages;
+    upd_blocks = (g.batch * g.hk * parts + kWaves - 1) / kWaves;
   }
   const int64_t units = (int64_t)g.batch * g.hq * a.xs;
   const unsigned blocks = (unsigned)((units + kWaves - 1) / kWaves + upd_blocks);

@@ -236,7 +236,7 @@ __device__ __forceinline__ void f32_to_words(const float* in, uint32_t* w) {
 
 // The step's own token, appended by the score block whose pages include it:
 // AppendKV and the digest update.  Alg. 2's current-page rule (last_loaded of the
-// token's page = step - 1) is applied by the selection (topk_role), which owns
+// token's page = step - 1) is applied by the selection (select_role), which owns
 // every last_loaded write of the step.
 template <typename T>
 struct StepToken {
@@ -381,40 +381,54 @@ __device__ __forceinline__ void score_role(const Geometry& g, int page0, int pag
   pre_barrier();
   __syncthreads();
 
-  float score[ITERS];
+  // every pass's digests as floats (widened where the token lands), then the
+  // heads one by one over all passes: a head's staged queries are read from LDS
+  // once per workgroup share instead of once per pass (the reads of every pass
+  // would keep the LDS as busy as the arithmetic keeps the vector units)
+  float lo[ITERS][S::VEC], hi[ITERS][S::VEC], score[ITERS];
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) {
     score[it] = 0.f;
-    const int wpage0 = page0 + (it * nw + wave) * S::PPW;
-    if (it > 0 && wpage0 >= page_end) break;  // uniform: no page of this pass
-    const int page = wpage0 + lane / S::LPP;
-    float lo[S::VEC], hi[S::VEC];
-    words_to_f32<T, S::WORDS>(raw[it][0], lo);
-    words_to_f32<T, S::WORDS>(raw[it][1], hi);
+    const int page = page0 + (it * nw + wave) * S::PPW + lane / S::LPP;
+    words_to_f32<T, S::WORDS>(raw[it][0], lo[it]);
+    words_to_f32<T, S::WORDS>(raw[it][1], hi[it]);
     if (has_tok && page == tok.lp) {  // widen (or start) the digest with the new key
       float kv[S::VEC];
       words_to_f32<T, S::WORDS>(kw, kv);
 #pragma unroll
       for (int v = 0; v < S::VEC; ++v) {
         if (tok.slot == 0) {
-          lo[v] = kv[v];
-          hi[v] = kv[v];
+          lo[it][v] = kv[v];
+          hi[it][v] = kv[v];
         } else {
-          if (kv[v] < lo[v]) lo[v] = kv[v];
-          if (hi[v] < kv[v]) hi[v] = kv[v];
+          if (kv[v] < lo[it][v]) lo[it][v] = kv[v];
+          if (hi[it][v] < kv[v]) hi[it][v] = kv[v];
         }
       }
       T* row = (DEFER ? dig_lds : drow + (int64_t)page * 2 * D) + c * S::VEC;
       uint32_t w[S::WORDS];
-      f32_to_words<T, S::WORDS>(lo, w);
+      f32_to_words<T, S::WORDS>(lo[it], w);
       store_words<S::WORDS>(row, w);
-      f32_to_words<T, S::WORDS>(hi, w);
+      f32_to_words<T, S::WORDS>(hi[it], w);
       store_words<S::WORDS>(row + D, w);
     }
-    float Ssum = 0.f;
-    // head gq's sum over d (a perfect binary tree: in-lane, then across the
-    // row's lanes), added to the running sum in head order
-    auto head = [&](int gq) {
+  }
+  // passes that hold a page of the share (wavefront-uniform)
+  const int wfirst = page0 + wave * S::PPW;
+  // head gq's sum over d (a perfect binary tree: in-lane, then across the
+  // row's lanes), added to the running sum in head order
+  auto head = [&](int gq) {
+    float qp[S::VEC], qn[S::VEC];
+#pragma unroll
+    for (int v = 0; v < S::VEC; v += 4) {
+      const float4 p4 = *reinterpret_cast<const float4*>(sq + gq * D + c * S::VEC + v);
+      const float4 n4 = *reinterpret_cast<const float4*>(sq + gd + gq * D + c * S::VEC + v);
+      qp[v] = p4.x, qp[v + 1] = p4.y, qp[v + 2] = p4.z, qp[v + 3] = p4.w;
+      qn[v] = n4.x, qn[v + 1] = n4.y, qn[v + 2] = n4.z, qn[v + 3] = n4.w;
+    }
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+      if (it > 0 && wfirst + it * nw * S::PPW >= page_end) break;  // uniform
       float t[S::VEC];
 #pragma unroll
       for (int v = 0; v < S::VEC; ++v) {
@@ -425,9 +439,7 @@ __device__ __forceinline__ void score_role(const Geometry& g, int page0, int pag
         // as the plain product does.  Only a zero term's sign can differ,
         // which changes no sum with a nonzero term and is cleared by the
         // final + 0.0f otherwise, so the score is the same bit for bit.
-        const float qp = sq[gq * D + c * S::VEC + v];
-        const float qn = sq[gd + gq * D + c * S::VEC + v];
-        t[v] = __builtin_fmaf(qn, lo[v], qp * hi[v]);
+        t[v] = __builtin_fmaf(qn[v], lo[it][v], qp[v] * hi[it][v]);
       }
 #pragma unroll
       for (int w = 1; w < S::VEC; w *= 2)
@@ -438,16 +450,17 @@ __device__ __forceinline__ void score_role(const Geometry& g, int page0, int pag
       s = s + dpp_f<kDppXor2>(s);
       s = s + dpp_f<kDppShl4>(s);
       s = s + dpp_f<kDppShl8>(s);
-      Ssum = (gq == 0) ? s : Ssum + s;
-    };
-    if constexpr (GC > 0) {
-#pragma unroll
-      for (int gq = 0; gq < GC; ++gq) head(gq);
-    } else {
-      for (int gq = 0; gq < g.G; ++gq) head(gq);
+      score[it] = (gq == 0) ? s : score[it] + s;
     }
-    score[it] = Ssum + 0.0f;
+  };
+  if constexpr (GC > 0) {
+#pragma unroll
+    for (int gq = 0; gq < GC; ++gq) head(gq);
+  } else {
+    for (int gq = 0; gq < g.G; ++gq) head(gq);
   }
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) score[it] = score[it] + 0.0f;
   if (!DEFER && has_tok && tid < D) {
     tok.k_row[tid] = tok_k;
     tok.v_col[(int64_t)tid * g.P] = tok_v;
@@ -469,10 +482,8 @@ __device__ __forceinline__ int budget_pages(const Geometry& g, int len) {
   return b / g.P;
 }
 
-// ============================================================================
-// Top-k + mask role: PageSelect and UpdateAndBuildMask (Alg. 1, Alg. 2) for
-// one (sequence, KV head); see topk.hip for the algorithm.
-// ============================================================================
+// Arguments of the selection of the multi-launch plans: PageSelect and
+// UpdateAndBuildMask (Alg. 1, Alg. 2); see select_role (threshold.h).
 struct TopkArgs {
   Geometry g;
   int step;
@@ -483,298 +494,15 @@ struct TopkArgs {
   int32_t* mask;
   int32_t* num_selected;
   int32_t* sel_phys;  // physical ids of the kept pages, or null
+  int update;         // 0: last_loaded is left as it is
+  int32_t* tok_out;   // [batch * h_k]: the token's page if it is not kept, else -1; or null
 };
-
-constexpr int kTopkBins = 2048;    // bins of an 11-bit digit
-constexpr int kTopkPasses = 3;     // 11 + 11 + 10 bits cover a 32-bit key
-constexpr int kTopkHistWords = kTopkPasses * kTopkBins;  // one histogram per pass
-constexpr int kTopkSmall = 32 + 4 + 256;  // ints: min/max exchange, pass result, per-(stripe, wave) counts
 
 __device__ __forceinline__ uint64_t wave_ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 // number of set bits of m in lanes below this one
 __device__ __forceinline__ int lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
-
-// The selection itself, without its outputs: returns k, the pages kept, and
-// calls `on_page(pos, p, a_old, phys)` for every stripe slot of every thread
-// (p: logical page, a_old: its last_loaded value as Alg. 2 reads it, phys: its
-// page-table entry; pos: its rank among the kept pages in page order, or -1
-// when it is not kept or past the sequence).
-// THREADS = blockDim.x threads (at most MAXW wavefronts); page i of the
-// sequence is held by thread i mod THREADS in stripe i / THREADS (coalesced
-// loads).  ceil(max_pages / THREADS) <= PER.  tok_lp: logical page written by
-// this step's token (-1: none), read after `len_of()` (which may set it):
-// Alg. 2's current-page rule applies to it, so its last_loaded entry is taken as
-// step - 1.  `len_of()` gives the sequence's length in tokens (with the step's
-// token when it is stored), which fixes n = its pages and the budget; it is called once
-// the loads are issued.  hist: kTopkHistWords
-// uint32 of LDS; small: kTopkSmall ints of LDS.
-// `wait()` is called after the page-table and last_loaded loads are issued and
-// before the scores are read.
-template <int PER, int MAXW, typename LenOf, typename Wait, typename OnPage>
-__device__ __forceinline__ int topk_core(const TopkArgs& ta, int bh, LenOf&& len_of, const int& tok_lp,
-                                         uint32_t* hist, int* small, Wait&& wait,
-                                         OnPage&& on_page) {
-  constexpr int NCH = (PER * MAXW + 63) / 64;  // 64-entry chunks of the count table
-  static_assert(PER * MAXW <= kTopkSmall - 36 && MAXW <= 16 && PER <= 32, "top-k shape");
-  const int THREADS = blockDim.x, NW = THREADS >> 6;
-  const Geometry& g = ta.g;
-  const int step = ta.step;
-  const int tid = thread_index(), lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int b = bh / g.hk;
-  const float* srow = ta.scores + (int64_t)bh * g.max_pages;
-  const int32_t* a_row = ta.A + (int64_t)bh * g.max_pages;
-  const int32_t* p_row = ta.pt + (int64_t)b * g.max_pages;
-  int* red = small;        // [32]
-  int* res = small + 32;   // [4]: T's digit, keys above its bin, keys in it
-  int* cnt = small + 36;   // [PER * NW]
-
-  // Loads are issued for every stripe slot before the number of pages is known
-  // (an in-bounds index stands in for slots past the row; their values are
-  // not used), so none waits for another.
-  const int last = g.max_pages - 1;
-  int32_t a_old[PER], phys[PER];
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const int idx = min(j * THREADS + tid, last);
-    a_old[j] = a_row[idx];
-    phys[j] = p_row[idx];
-  }
-  for (int i = tid; i < kTopkHistWords; i += THREADS) hist[i] = 0u;
-  wait();
-  float sv[PER];  // device-coherent loads: the scores may come from other XCDs of this launch
-#pragma unroll
-  for (int j = 0; j < PER; ++j)
-    sv[j] = __hip_atomic_load(srow + min(j * THREADS + tid, last), __ATOMIC_RELAXED,
-                              __HIP_MEMORY_SCOPE_AGENT);
-  const int len = len_of();
-  const int n = min((len + g.P - 1) / g.P, g.max_pages);
-  auto valid = [&](int j) { return j * THREADS + tid < n; };
-#pragma unroll
-  for (int j = 0; j < PER; ++j)
-    if (j * THREADS + tid == tok_lp) a_old[j] = step - 1;
-  uint32_t key[PER];
-#pragma unroll
-  for (int j = 0; j < PER; ++j) key[j] = valid(j) ? order_key(sv[j]) : 0u;
-
-  // rel = key - kmin over the valid keys; T is searched among rel values.
-  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-#pragma unroll
-  for (int j = 0; j < PER; ++j)
-    if (valid(j)) {
-      kmin = min(kmin, key[j]);
-      kmax = max(kmax, key[j]);
-    }
-  kmin = wave_umin(kmin);
-  kmax = wave_umax(kmax);
-  if (lane == 0) {
-    red[wave] = (int)kmin;
-    red[16 + wave] = (int)kmax;
-  }
-  __syncthreads();  // also orders the histogram clearing before the first pass
-  kmin = wave_umin(lane < NW ? (uint32_t)red[lane] : 0xFFFFFFFFu);
-  kmax = wave_umax(lane < NW ? (uint32_t)red[16 + lane] : 0u);
-  const uint32_t range = kmax - kmin;
-  const int nbits = range ? 32 - __clz((int)range) : 1;
-  const int k = min(min(budget_pages(g, len), n), g.k_max);
-
-  // Radix select: pass p histograms the next digit of the keys that still match
-  // T's prefix into its own histogram.  After a barrier, wavefront 0 alone
-  // scans it (descending bins, lane l owning 32 of them) and publishes T's
-  // digit, the keys above its bin and the keys in it; the other wavefronts
-  // wait at the next barrier (a scan by every wavefront would share the four
-  // SIMDs between sixteen copies of the same work).
-  uint64_t prefix = 0u;  // digits of T's rel fixed so far, bits [lo, nbits)
-  int lo = nbits;
-  uint32_t need = (uint32_t)k;  // keys still to take among those matching the prefix
-  if (k > 0 && k < n) {
-    int pass = 0;
-#pragma unroll 1
-    for (int hi = nbits; hi > 0; hi = lo, ++pass) {
-      lo = max(hi - 11, 0);
-      uint32_t* h = hist + pass * kTopkBins;
-      const uint32_t dmask = (1u << (hi - lo)) - 1u;
-#pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const uint64_t rel = key[j] - kmin;
-        if (valid(j) && (rel >> hi) == prefix) atomicAdd(&h[(rel >> lo) & dmask], 1u);
-      }
-      __syncthreads();
-      if (wave == 0) {
-        const int base = kTopkBins - 32 * (lane + 1);
-        uint32_t gs[8];  // totals of this lane's eight 4-bin groups (ascending bins)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const uint4 u = *reinterpret_cast<const uint4*>(h + base + 4 * i);
-          gs[i] = u.x + u.y + u.z + u.w;
-        }
-        uint32_t own = 0u;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) own += gs[i];
-        const uint32_t incl = (uint32_t)wave_inclusive_scan((int)own);
-        uint32_t acc = incl - own;  // keys in higher bins
-        const bool hit = acc < need && need <= incl;
-        // the group holding T's digit (highest group first), then the bin in it
-        int fgrp = 0;
-        uint32_t facc = 0u;
-        bool found = false;
-#pragma unroll
-        for (int i = 7; i >= 0; --i) {
-          const bool f = !found && acc + gs[i] >= need;
-          fgrp = f ? i : fgrp;
-          facc = f ? acc : facc;
-          found = found || f;
-          acc += gs[i];
-        }
-        const uint4 u = *reinterpret_cast<const uint4*>(h + base + 4 * fgrp);
-        const uint32_t gv[4] = {u.x, u.y, u.z, u.w};
-        int fb = 0;
-        uint32_t fc = 0u, fa = 0u;
-        found = false;
-        acc = facc;
-#pragma unroll
-        for (int i = 3; i >= 0; --i) {
-          const bool f = !found && acc + gv[i] >= need;
-          fb = f ? base + 4 * fgrp + i : fb;
-          fc = f ? gv[i] : fc;
-          fa = f ? acc : fa;
-          found = found || f;
-          acc += gv[i];
-        }
-        if (hit) {  // exactly one lane: need lies in its range of the running total
-          res[0] = fb;
-          res[1] = (int)fa;
-          res[2] = (int)fc;
-        }
-      }
-      __syncthreads();
-      const int bin = res[0];
-      const uint32_t above = (uint32_t)res[1], inbin = (uint32_t)res[2];
-      need -= above;
-      prefix = (prefix << (hi - lo)) | (uint32_t)bin;
-      if (inbin == need) break;  // T's whole bin is kept: its prefix suffices
-      if (lo > 0 && inbin <= 64) {
-        // T is one of its bin's few keys: list them (in the next pass's
-        // histogram, still zero) and let wavefront 0 rank them exactly (lane i
-        // holds candidate i and counts the larger and equal ones through LDS
-        // broadcast reads) instead of histogramming further digits.
-        uint32_t* cand = hist + (pass + 1) * kTopkBins;  // [0]: count, [1..]: rel values
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-          const uint64_t rel = key[j] - kmin;
-          if (valid(j) && (rel >> lo) == prefix) cand[1 + atomicAdd(&cand[0], 1u)] = (uint32_t)rel;
-        }
-        __syncthreads();
-        if (wave == 0) {
-          const uint32_t v = lane < (int)inbin ? cand[1 + lane] : 0u;
-          uint32_t gt = 0u, eq = 0u;
-          for (int j2 = 0; j2 < (int)inbin; ++j2) {
-            const uint32_t w = cand[1 + j2];
-            gt += w > v ? 1u : 0u;
-            eq += w == v ? 1u : 0u;
-          }
-          const bool is_t = lane < (int)inbin && gt < need && need <= gt + eq;
-          if (lane == __builtin_ctzll(wave_ballot(is_t))) {
-            res[0] = (int)v;   // T's whole rel
-            res[1] = (int)gt;  // candidates above T
-          }
-        }
-        __syncthreads();
-        prefix = (uint32_t)res[0];
-        need -= (uint32_t)res[1];  // keys equal to T still to take
-        lo = 0;
-        break;
-      }
-    }
-  }
-
-  // Compaction in page order.  A kept page's output slot is the number of kept
-  // pages below it: pages above T's prefix all count, pages tying with it count
-  // up to `need` (lower page indices first).  Per stripe, ballots give the
-  // counts below a lane inside its wavefront; an exclusive scan over the
-  // (stripe, wavefront) count table, in page order, gives the rest.
-  const bool all = k >= n;
-  const bool some = k > 0 && k < n;
-  uint32_t gt_bits = 0u, eq_bits = 0u;  // per stripe: above T's prefix / tying with it
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const uint64_t km = (uint64_t)(key[j] - kmin) >> lo;
-    const bool v = valid(j);
-    const bool gt = v && (all || (some && km > prefix));
-    const bool eq = v && some && km == prefix;
-    gt_bits |= (gt ? 1u : 0u) << j;
-    eq_bits |= (eq ? 1u : 0u) << j;
-    const int cg = __popcll(wave_ballot(gt)), ce = __popcll(wave_ballot(eq));
-    if (lane == 0) cnt[j * NW + wave] = cg | (ce << 16);
-  }
-  __syncthreads();
-  int sc[NCH];  // exclusive scan of the count table, entry c * 64 + lane
-  int carry = 0;
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int e = c * 64 + lane;
-    const int val = e < PER * NW ? cnt[e] : 0;
-    const int incl = wave_inclusive_scan(val) + carry;
-    sc[c] = incl - val;
-    carry = __builtin_amdgcn_readlane(incl, 63);
-  }
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const int e = j * NW + wave;
-    int below = 0;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
-      if (e / 64 == c) below = __builtin_amdgcn_readlane(sc[c], e % 64);
-    const bool is_gt = (gt_bits >> j) & 1u;
-    const bool is_eq = (eq_bits >> j) & 1u;
-    const int gb = (below & 0xFFFF) + lanes_below(wave_ballot(is_gt));
-    const int eb = (below >> 16) + lanes_below(wave_ballot(is_eq));
-    int pos = -1;
-    if (is_gt) pos = gb + min(eb, (int)need);
-    if (is_eq && eb < (int)need) pos = gb + eb;
-    // pos < k always holds for a kept page; the test guards the writes
-    on_page(pos < k ? pos : -1, j * THREADS + tid, a_old[j], phys[j]);
-  }
-  return k;
-}
-
-// Selection of KV head bh with its outputs: the selected pages in page order,
-// their mask values M (last_loaded before the step) and physical pages, -1
-// past the k kept ones, the count, and last_loaded set to the step for the kept
-// pages (step - 1 for the token's page when it is not kept).  Arguments as
-// topk_core's.  COH: the selection is read by other workgroups of the same
-// launch, so it is stored device-coherently.
-template <int PER, int MAXW, bool COH, typename LenOf, typename Wait>
-__device__ __forceinline__ void topk_role(const TopkArgs& ta, int bh, LenOf&& len_of, int tok_lp,
-                                          uint32_t* hist, int* small, Wait&& wait) {
-  const Geometry& g = ta.g;
-  const int step = ta.step;
-  int32_t* a_row = ta.A + (int64_t)bh * g.max_pages;
-  int32_t* sel_row = ta.selected + (int64_t)bh * g.k_max;
-  int32_t* m_row = ta.mask + (int64_t)bh * g.k_max;
-  int32_t* ph_row = ta.sel_phys ? ta.sel_phys + (int64_t)bh * g.k_max : nullptr;
-  const int k = topk_core<PER, MAXW>(
-      ta, bh, len_of, tok_lp, hist, small, wait, [&](int pos, int p, int a_old, int phys) {
-        if (pos >= 0) {
-          put_c<COH>(sel_row + pos, p);
-          put_c<COH>(m_row + pos, a_old);
-          a_row[p] = step;
-          if (ph_row) put_c<COH>(ph_row + pos, (phys >= 0 && phys < g.num_phys) ? phys : -1);
-        } else if (p == tok_lp) {
-          a_row[p] = step - 1;  // the token's page, not kept
-        }
-      });
-  const int tid = thread_index(), THREADS = blockDim.x;
-  for (int i = k + tid; i < g.k_max; i += THREADS) {
-    put_c<COH>(sel_row + i, -1);
-    put_c<COH>(m_row + i, -1);
-    if (ph_row) put_c<COH>(ph_row + i, -1);
-  }
-  if (tid == 0) put_c<COH>(ta.num_selected + bh, k);
-}
-
 
 // ============================================================================
 // Attention role (see attend.hip for the design).
@@ -823,6 +551,11 @@ AttendArgs make_attend_args(const Geometry& g, int step, const void* q_window,
                             const retro_kv_cache& c, const retro_selection& sel,
                             const int32_t* sel_phys, float* o_ws, float* l_ws, const void* dummy);
 
+// The attention launch of bf16 layers outside the one-launch step
+// (stream_attend.hip); a.g from attend_geometry.
+// With `ta` its workgroups make the selection themselves (max_pages <= 6144).
+hipError_t launch_stream_attend(const AttendArgs& a, const TopkArgs* ta, hipStream_t s);
+
 
 // The attention pass of one (sequence, KV head, row group, split).  Row-tile
 // state and the query operands are set up first; `wait()` is then called (the
@@ -836,10 +569,9 @@ AttendArgs make_attend_args(const Geometry& g, int step, const void* q_window,
 // the same launch: device-coherent loads and stores.
 // The split's page list comes from the selection rows in memory (COH: written
 // by other workgroups of the same launch) when `list` is a SelectionRows, else
-// `list(tid, first, lp, m, phys)` gives thread tid's slot of it (slot tid of
-// the selection row from `first` on: logical page, mask value, physical page;
-// left as passed in for tid >= pages_per_split) and returns the number of
-// selected pages of the row.
+// `list(tid, lp, m, phys)` gives thread tid's slot of the split's page list
+// (logical page, mask value, physical page; left as passed in past the list)
+// and returns the number of selected pages of the head.
 // tok_pos >= 0: the position of the step's token, which another workgroup of
 // the same launch is storing into the cache: its key row and value column are
 // taken from a.tok_k / a.tok_v into LDS instead (so no gather has to wait for
@@ -948,7 +680,7 @@ __device__ __forceinline__ void attend_role(const AttendArgs& a, int b, int h, i
   } else if constexpr (kPreset) {
     k_eff = *list.k;
   } else {
-    k_eff = list(tid, first, lp, m, phys);
+    k_eff = list(tid, lp, m, phys);
   }
   const int seq_len = seq_len_of();
   const int np = min(g.pages_per_split, k_eff - first);
@@ -1359,9 +1091,6 @@ struct MergeArgs {
   int32_t* a_upd;
   const int32_t* sel_upd;
   const int32_t* tok_upd;
-  // sticky error word of the launch that produced the partials (a bounded wait
-  // ran out there), or null: when set, the rows are written as NaN
-  const int32_t* err;
 };
 
 template <int D>
@@ -1612,22 +1341,6 @@ __device__ __forceinline__ void merge_unit(const MergeArgs& a, const UnitPos& up
   // it is overwritten
   asm volatile("" : : "v"(merged.z) : "memory");
   put<D>(a.o_cache, a.l_cache, slot, p[1]);
-}
-
-// The output rows merge unit `unit` writes, as NaN; nothing else is written
-// (the output cache keeps its rows).
-template <int D>
-__device__ __forceinline__ void poison_unit(const MergeArgs& a, const UnitPos& up) {
-  const Geometry& g = a.g;
-  const int x = up.x, gq = up.gq, h = up.h, b = up.b;
-  const int qh = h * g.G + gq;
-  const int64_t out_row = (int64_t)b * (g.W + 1);
-  Row<D> p;
-#pragma unroll
-  for (int e = 0; e < Row<D>::E; ++e) p.o[e] = __builtin_nanf("");
-  p.z = __builtin_nanf("");
-  put<D>(a.o_out, a.l_out, (out_row + x) * g.hq + qh, p);
-  if (x == 0 && g.W > 0) put<D>(a.o_out, a.l_out, (out_row + g.W) * g.hq + qh, p);
 }
 
 MergeArgs make_merge_args(const Geometry& g, int step, int mode, const float* o_ws,

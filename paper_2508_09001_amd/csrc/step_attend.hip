@@ -78,6 +78,22 @@
 namespace retro {
 namespace {
 
+// The output rows merge unit `unit` writes, as NaN; nothing else is written
+// (the output cache keeps its rows).
+template <int D>
+__device__ __forceinline__ void poison_unit(const MergeArgs& a, const UnitPos& up) {
+  const Geometry& g = a.g;
+  const int x = up.x, gq = up.gq, h = up.h, b = up.b;
+  const int qh = h * g.G + gq;
+  const int64_t out_row = (int64_t)b * (g.W + 1);
+  Row<D> p;
+#pragma unroll
+  for (int e = 0; e < Row<D>::E; ++e) p.o[e] = __builtin_nanf("");
+  p.z = __builtin_nanf("");
+  put<D>(a.o_out, a.l_out, (out_row + x) * g.hq + qh, p);
+  if (x == 0 && g.W > 0) put<D>(a.o_out, a.l_out, (out_row + g.W) * g.hq + qh, p);
+}
+
 constexpr int kThreads = 512;
 constexpr uint64_t kEpochs = 0x7FFFFFFFull;  // epochs 1 .. 2^31 - 1
 constexpr int kWaves = kThreads / 64;

@@ -226,4 +226,91 @@ __device__ __forceinline__ void threshold_select(ThrLds<PER, NW>& L, const uint3
   }
 }
 
+// The selection of KV head bh by a workgroup of NW wavefronts (at most PER * NW
+// * 64 pages).  len: the sequence's tokens, the step's token included when it
+// is stored; tok_lp: that token's logical page (-1: none), for which Alg. 2's
+// current-page rule gives last_loaded = step - 1.  Every kept page goes to
+// `kept(slot, page, mask, phys)`: its rank in page order, logical page, mask value
+// M (last_loaded before the step) and physical page (-1: not mapped).  With
+// `write` the selection rows (-1 past the kept pages) and the count are stored,
+// and with ta.update last_loaded is set to the step for the kept pages (step - 1
+// for the token's page when it is not kept); else, with ta.tok_out, tok_out[bh]
+// = the token's page if it is not kept, -1 otherwise, for a later launch's
+// update.  Returns the number of kept pages.  The scores are read
+// device-coherently: they may come from other workgroups of the launch.
+template <int PER, int NW, typename Kept>
+__device__ __forceinline__ int select_role(const TopkArgs& ta, int bh, int len, int tok_lp,
+                                           ThrLds<PER, NW>& L, bool write, Kept&& kept) {
+  constexpr int NTS = 64 * NW;
+  const Geometry& g = ta.g;
+  const int tid = thread_index(), b = bh / g.hk, last = g.max_pages - 1;
+  const float* srow = ta.scores + (int64_t)bh * g.max_pages;
+  int32_t* a_row = ta.A + (int64_t)bh * g.max_pages;
+  const int32_t* p_row = ta.pt + (int64_t)b * g.max_pages;
+  // every load before any wait (an in-bounds index stands in past the row)
+  float sv[PER];
+  int32_t a_old[PER], phys[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int idx = min(j * NTS + tid, last);
+    sv[j] = __hip_atomic_load(srow + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    a_old[j] = a_row[idx];
+    phys[j] = p_row[idx];
+  }
+  thr_clear(L);  // the barrier before the first use is threshold_select's own
+  const int n = min((len + g.P - 1) / g.P, g.max_pages);
+  const int k = min(min(budget_pages(g, len), n), g.k_max);
+  uint32_t key[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) key[j] = order_key(sv[j]);
+  int pos[PER];
+  threshold_select<PER, NW, NTS>(L, key, n, k, pos);
+  int32_t* sel_row = ta.selected + (int64_t)bh * g.k_max;
+  int32_t* m_row = ta.mask + (int64_t)bh * g.k_max;
+  int32_t* ph_row = ta.sel_phys ? ta.sel_phys + (int64_t)bh * g.k_max : nullptr;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int p = j * NTS + tid, q = pos[j];
+    const int m = p == tok_lp ? ta.step - 1 : a_old[j];
+    const int ph = (phys[j] >= 0 && phys[j] < g.num_phys) ? phys[j] : -1;
+    if (q >= 0) kept(q, p, m, ph);
+    if (write) {
+      if (q >= 0) {
+        sel_row[q] = p;
+        m_row[q] = m;
+        if (ph_row) ph_row[q] = ph;
+        if (ta.update) a_row[p] = ta.step;
+      }
+      if (p == tok_lp) {
+        if (ta.update && q < 0) a_row[p] = ta.step - 1;
+        if (ta.tok_out) ta.tok_out[bh] = q < 0 ? p : -1;
+      }
+    }
+  }
+  if (write) {
+    for (int i = k + tid; i < g.k_max; i += NTS) {
+      sel_row[i] = -1;
+      m_row[i] = -1;
+      if (ph_row) ph_row[i] = -1;
+    }
+    if (tid == 0) {
+      ta.num_selected[bh] = k;
+      if (ta.tok_out && tok_lp < 0) ta.tok_out[bh] = -1;
+    }
+  }
+  return k;
+}
+
+// Pages per thread of a 512-thread workgroup's selection, at most, and the
+// instantiation for a table (f gets it as an integral_constant).
+constexpr int kSelectPer = 12;
+template <typename F>
+auto with_select_per(int max_pages, F&& f) {
+  constexpr int TH = 512;
+  if (max_pages <= TH * 2) return f(std::integral_constant<int, 2>{});
+  if (max_pages <= TH * 5) return f(std::integral_constant<int, 5>{});
+  if (max_pages <= TH * 9) return f(std::integral_constant<int, 9>{});
+  return f(std::integral_constant<int, kSelectPer>{});
+}
+
 }  // namespace retro

@@ -1,28 +1,8 @@
-// PageSelect + UpdateAndBuildMask (Alg. 1, Alg. 2) for one (sequence, KV head) per
-// workgroup.
-//
-// 1. Page i of the sequence belongs to thread i mod THREADS (stripe i /
-//    THREADS), so every load is coalesced.  Page-table entries, last_loaded
-//    values and scores (mapped to order-preserving 32-bit keys: larger float ->
-//    larger key, -0 == +0) are all requested before any is used.
-// 2. Radix select over rel = key - min_key with 11-bit digits taken from the
-//    top of rel's actual bit length.  Each pass histograms the digit of the
-//    keys still in the running into a histogram of its own (so none is cleared
-//    between passes); one wavefront scans it (a prefix sum over its lanes' bin
-//    totals locates T, the k-th largest key) and publishes T's digit through
-//    LDS, and `need` becomes the number of keys to take from T's bin.  The
-//    search stops as soon as that bin is taken whole or all bits are fixed;
-//    a bin of at most 64 keys is instead listed in LDS and ranked exactly by
-//    one wavefront.
-// 3. Compaction in page order: a page is kept if its rel is above T's prefix,
-//    or ties with it and is among the first `need` such pages (ties go to the
-//    lower page index).  Ballots count kept pages below a lane within its
-//    wavefront and stripe; one scan over the (stripe, wavefront) table, which
-//    is in page order, adds the pages below in other wavefronts and stripes.
-// 4. Alg. 2 for the kept pages: mask = last_loaded[p]; last_loaded[p] = step.
-//    Kept pages are distinct, so each thread updates its own.  The physical page
-//    of every kept page is written too (for the attention kernel).
-#include "roles.h"
+// PageSelect + UpdateAndBuildMask (Alg. 1, Alg. 2) as a launch of its own, one
+// workgroup per (sequence, KV head), for tables longer than the score and
+// attention launches' own selection takes.  The selection is select_role
+// (threshold.h).
+#include "threshold.h"
 
 namespace retro {
 namespace {
@@ -30,20 +10,16 @@ namespace {
 template <int THREADS, int PER>
 __global__ void __launch_bounds__(THREADS) topk_mask_kernel(TopkArgs ta,
                                                             const int32_t* __restrict__ seq_lens) {
-  __shared__ __attribute__((aligned(16))) uint32_t hist[kTopkHistWords];
-  __shared__ int small[kTopkSmall];
+  __shared__ __attribute__((aligned(16))) ThrLds<PER, THREADS / 64> L;
   const int bh = blockIdx.x;
   const int b = bh / ta.g.hk;
   // a pending token (Geometry::token_pending) gets Alg. 2's current-page rule here
-  int tok_lp = -1;
-  if (ta.g.token_pending) {
-    const int pos = seq_lens[b];
-    if (token_phys(ta.g, ta.pt, b, pos) >= 0) tok_lp = pos / ta.g.P;
+  int tok_lp = -1, len = seq_lens[b];
+  if (ta.g.token_pending && token_phys(ta.g, ta.pt, b, len) >= 0) {
+    tok_lp = len / ta.g.P;
+    len += 1;
   }
-  topk_role<PER, THREADS / 64, false>(
-      ta, bh,
-      [&] { return live_seq_len(ta.g, seq_lens, ta.pt, b); },
-      tok_lp, hist, small, [] {});
+  select_role<PER, THREADS / 64>(ta, bh, len, tok_lp, L, true, [](int, int, int, int) {});
 }
 
 // Alg. 2 on the kept selection of a top-k reuse step: one wavefront per
@@ -85,16 +61,10 @@ hipError_t launch_topk_mask(const Geometry& g, int step, const float* scores,
                             const retro_kv_cache& c, const retro_selection& sel,
                             int32_t* sel_phys, hipStream_t s) {
   TopkArgs ta{g, step, scores, c.page_table, c.last_loaded, sel.selected, sel.mask,
-              sel.num_selected, sel_phys};
+              sel.num_selected, sel_phys, 1, nullptr};
   const unsigned grid = (unsigned)(g.batch * g.hk);
-  // one workgroup per head: its time is one wavefront's instruction count,
-  // so sixteen wavefronts share the pages
-  if (g.max_pages <= 1024 * 3)
-    topk_mask_kernel<1024, 3><<<grid, 1024, 0, s>>>(ta, c.seq_lens);
-  else if (g.max_pages <= 1024 * 6)
-    topk_mask_kernel<1024, 6><<<grid, 1024, 0, s>>>(ta, c.seq_lens);
-  else
-    topk_mask_kernel<1024, 16><<<grid, 1024, 0, s>>>(ta, c.seq_lens);
+  // one workgroup per head: sixteen wavefronts share the pages (at most 16384)
+  topk_mask_kernel<1024, 16><<<grid, 1024, 0, s>>>(ta, c.seq_lens);
   return hipGetLastError();
 }
 
