@@ -168,55 +168,98 @@ __global__ void __launch_bounds__(kAppendThreads) append_tokens_kernel(
   if (n_ok > 0 && threadIdx.x == 0) seq_lens[b] = pos0 + n_ok;
 }
 
-// Prefill, pass 1: one workgroup per token copies its keys (token-major page) and
-// values (d-major page).
-template <typename T>
-__global__ void __launch_bounds__(256) prefill_write_kernel(Geometry g, int seq, int start,
-                                                            T* __restrict__ kc,
-                                                            T* __restrict__ vc,
-                                                            const int32_t* __restrict__ pt,
-                                                            const T* __restrict__ k_src,
-                                                            const T* __restrict__ v_src) {
-  const int j = blockIdx.x;
-  const int pos = start + j;
-  const int lp = pos / g.P, slot = pos - lp * g.P;
-  if (lp >= g.max_pages) return;
-  const int phys = pt[(int64_t)seq * g.max_pages + lp];
-  if (phys < 0 || phys >= g.num_phys) return;
-  const int n = g.hk * g.D;
-  for (int e = threadIdx.x; e < n; e += blockDim.x) {
-    const int h = e / g.D, i = e - h * g.D;
-    const int64_t ph = (int64_t)phys * g.hk + h;
-    kc[(ph * g.P + slot) * g.D + i] = k_src[(int64_t)j * n + e];
-    vc[(ph * g.D + i) * g.P + slot] = v_src[(int64_t)j * n + e];
-  }
-}
+// Prefill: one workgroup per (touched page, KV head) stores the page's new keys
+// (token-major) and values (d-major, transposed through LDS, whole 16-byte
+// pieces) and its digest, the element-wise min / max over all of its stored
+// keys, from the keys in LDS (those of earlier calls read back from the cache).
+// Bound by HBM: every key and value is read and written once.  VEC: sources and
+// caches are 16-byte aligned; otherwise element by element.  30011 tokens of 8
+// heads, d 128, bf16 in chunks of 8192 (254 MB): 212 us as a launch per token
+// with 2-byte scattered value stores and a second launch over the stored keys.
+constexpr int kPrefillThreads = 128;
 
-// Prefill, pass 2: digest of every touched page = min / max over its stored slots.
-template <typename T>
-__global__ void __launch_bounds__(128) prefill_digest_kernel(Geometry g, int seq, int start,
-                                                             int end, const T* __restrict__ kc,
-                                                             T* __restrict__ dg,
-                                                             const int32_t* __restrict__ pt,
-                                                             int32_t* __restrict__ seq_lens) {
-  const int lp = start / g.P + blockIdx.x;
-  const int h = blockIdx.y;
-  if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0) seq_lens[seq] = end;
+template <typename T, int PS, int D, bool VEC>
+__global__ void __launch_bounds__(kPrefillThreads) prefill_kernel(
+    Geometry g, int seq, int start, int end, T* __restrict__ kc, T* __restrict__ vc,
+    T* __restrict__ dg, const int32_t* __restrict__ pt, int32_t* __restrict__ seq_lens,
+    const T* __restrict__ k_src, const T* __restrict__ v_src) {
+  constexpr int E = 16 / sizeof(T);   // elements of a 16-byte piece
+  constexpr int ROW = D + E;          // padded LDS row
+  constexpr int PPR = D / E;          // pieces of a token's row
+  constexpr int NP = PS * PPR / kPrefillThreads;
+  static_assert(PS * PPR % kPrefillThreads == 0, "whole passes over the page's pieces");
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) T ks[PS * ROW];
+  __shared__ __attribute__((aligned(16))) T vs[PS * ROW];
+  const int tid = threadIdx.x, h = blockIdx.y;
+  const int lp = start / PS + blockIdx.x;
+  if (blockIdx.x == 0 && h == 0 && tid == 0) seq_lens[seq] = end;
   if (lp >= g.max_pages) return;
   const int phys = pt[(int64_t)seq * g.max_pages + lp];
   if (phys < 0 || phys >= g.num_phys) return;
-  const int filled = min(g.P, end - lp * g.P);
-  const int64_t ph = (int64_t)phys * g.hk + h;
-  T* drow = dg + ((((int64_t)seq * g.hk + h) * g.max_pages + lp) * 2) * g.D;
-  for (int i = threadIdx.x; i < g.D; i += blockDim.x) {
-    T lo = kc[(ph * g.P) * g.D + i], hi = lo;
-    for (int s = 1; s < filled; ++s) {
-      const T v = kc[(ph * g.P + s) * g.D + i];
+  const int s0 = max(start - lp * PS, 0), s1 = min(end - lp * PS, PS);  // slots stored here
+  const int64_t blk = ((int64_t)phys * g.hk + h) * PS * D;
+  const int64_t src0 = ((int64_t)(lp * PS - start) * g.hk + h) * D;  // slot 0's row of the sources
+  const int64_t stride = (int64_t)g.hk * D;
+  if constexpr (VEC) {
+    u32x4 kr[NP], vr[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int e = tid + i * kPrefillThreads, t = e / PPR, c = e % PPR * E;
+      if (t >= s0 && t < s1) {
+        kr[i] = *reinterpret_cast<const u32x4*>(k_src + src0 + t * stride + c);
+        vr[i] = *reinterpret_cast<const u32x4*>(v_src + src0 + t * stride + c);
+      } else if (t < s0) {  // stored by an earlier call
+        kr[i] = *reinterpret_cast<const u32x4*>(kc + blk + t * D + c);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int e = tid + i * kPrefillThreads, t = e / PPR, c = e % PPR * E;
+      if (t >= s1) continue;
+      *reinterpret_cast<u32x4*>(ks + t * ROW + c) = kr[i];
+      if (t < s0) continue;
+      *reinterpret_cast<u32x4*>(vs + t * ROW + c) = vr[i];
+      *reinterpret_cast<u32x4*>(kc + blk + t * D + c) = kr[i];
+    }
+  } else {
+    for (int e = tid; e < s1 * D; e += kPrefillThreads) {
+      const int t = e / D, i = e - t * D;
+      const T k = t < s0 ? kc[blk + e] : k_src[src0 + t * stride + i];
+      ks[t * ROW + i] = k;
+      if (t < s0) continue;
+      vs[t * ROW + i] = v_src[src0 + t * stride + i];
+      kc[blk + e] = k;
+    }
+  }
+  __syncthreads();
+  // values: E consecutive tokens of one element of d per piece
+  for (int e = tid; e < D * (PS / E); e += kPrefillThreads) {
+    const int i = e % D, t0 = e / D * E;
+    T* dst = vc + blk + (int64_t)i * PS + t0;
+    T v[E];
+#pragma unroll
+    for (int q = 0; q < E; ++q) v[q] = vs[(t0 + q) * ROW + i];
+    if (VEC && t0 >= s0 && t0 + E <= s1) {
+      u32x4 u;
+      __builtin_memcpy(&u, v, 16);
+      *reinterpret_cast<u32x4*>(dst) = u;
+    } else {
+#pragma unroll
+      for (int q = 0; q < E; ++q)
+        if (t0 + q >= s0 && t0 + q < s1) dst[q] = v[q];
+    }
+  }
+  T* drow = dg + ((((int64_t)seq * g.hk + h) * g.max_pages + lp) * 2) * D;
+  for (int i = tid; i < D; i += kPrefillThreads) {
+    T lo = ks[i], hi = lo;
+    for (int t = 1; t < s1; ++t) {
+      const T v = ks[t * ROW + i];
       if (less(v, lo)) lo = v;
       if (less(hi, v)) hi = v;
     }
     drow[i] = lo;
-    drow[g.D + i] = hi;
+    drow[D + i] = hi;
   }
 }
 
@@ -326,17 +369,27 @@ template <typename T>
 hipError_t prefill_t(const Geometry& g, const retro_kv_cache& c, int seq, int start, int n,
                      const void* k_src, const void* v_src, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  prefill_write_kernel<T><<<n, 256, 0, s>>>(g, seq, start, (T*)c.k_cache, (T*)c.v_cache,
-                                            c.page_table, (const T*)k_src, (const T*)v_src);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const int end = start + n;
-  const int pages = (end - 1) / g.P - start / g.P + 1;
-  prefill_digest_kernel<T><<<dim3(pages, g.hk), 128, 0, s>>>(g, seq, start, end,
-                                                             (const T*)c.k_cache,
-                                                             (T*)c.digest, c.page_table,
-                                                             c.seq_lens);
-  return hipGetLastError();
+  const dim3 grid((unsigned)((end - 1) / g.P - start / g.P + 1), (unsigned)g.hk);
+  const bool vec = ((reinterpret_cast<uintptr_t>(k_src) | reinterpret_cast<uintptr_t>(v_src) |
+                     reinterpret_cast<uintptr_t>(c.k_cache) |
+                     reinterpret_cast<uintptr_t>(c.v_cache)) & 15u) == 0;
+  auto go = [&](auto ps, auto d, auto v) {
+    prefill_kernel<T, decltype(ps)::value, decltype(d)::value, decltype(v)::value>
+        <<<grid, kPrefillThreads, 0, s>>>(g, seq, start, end, (T*)c.k_cache, (T*)c.v_cache,
+                                          (T*)c.digest, c.page_table, c.seq_lens,
+                                          (const T*)k_src, (const T*)v_src);
+    return hipGetLastError();
+  };
+  auto with_d = [&](auto ps, auto v) {
+    return g.D == 128 ? go(ps, std::integral_constant<int, 128>{}, v)
+                      : go(ps, std::integral_constant<int, 64>{}, v);
+  };
+  auto with_ps = [&](auto v) {
+    return g.P == 16 ? with_d(std::integral_constant<int, 16>{}, v)
+                     : with_d(std::integral_constant<int, 32>{}, v);
+  };
+  return vec ? with_ps(std::true_type{}) : with_ps(std::false_type{});
 }
 
 }  // namespace
