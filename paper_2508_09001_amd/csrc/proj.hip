@@ -34,29 +34,58 @@ __device__ __forceinline__ uint16_t bf16_rne(float x) {
   return static_cast<uint16_t>((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
 
-__device__ __forceinline__ bf16x8 bits_to_bf16x8(uint4 u) {
-  return __builtin_bit_cast(bf16x8, u);
+// Row operands.  A wavefront loads a 16-row x 32-element tile of x with four
+// consecutive lanes on one row (64 bytes of bf16; in operand order, lane % 16
+// being the row, four consecutive lanes would touch four rows and the load take
+// four times as long), converts f32 rows to bf16, and turns it into operand
+// order through 1 KB of LDS of its own; the pieces of a row are stored permuted
+// so that neither access meets bank conflicts.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+template <bool F32IN>
+struct RowRaw {
+  u32x4 v[F32IN ? 2 : 1];
+};
+
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
 }
 
-// A operand: row `row` of x, elements [k, k + 8); zero past the last row.
-// x is bf16 [rows][K], or f32 [rows][K] rounded to bf16 here.
-template <bool F32IN>
-__device__ __forceinline__ bf16x8 load_a(const void* x, int rows, int K, int row, int k) {
-  if (row >= rows) return bits_to_bf16x8(make_uint4(0, 0, 0, 0));
-  if constexpr (F32IN) {
-    const float* p = static_cast<const float*>(x) + (int64_t)row * K + k;
-    const float4 lo = *reinterpret_cast<const float4*>(p);
-    const float4 hi = *reinterpret_cast<const float4*>(p + 4);
-    uint4 u;
-    u.x = bf16_rne(lo.x) | (uint32_t(bf16_rne(lo.y)) << 16);
-    u.y = bf16_rne(lo.z) | (uint32_t(bf16_rne(lo.w)) << 16);
-    u.z = bf16_rne(hi.x) | (uint32_t(bf16_rne(hi.y)) << 16);
-    u.w = bf16_rne(hi.z) | (uint32_t(bf16_rne(hi.w)) << 16);
-    return bits_to_bf16x8(u);
-  } else {
-    const bf16_t* p = static_cast<const bf16_t*>(x) + (int64_t)row * K + k;
-    return bits_to_bf16x8(*reinterpret_cast<const uint4*>(p));
+// this lane's piece of a tile: row lane / 4 of the 16 from row0, elements
+// [k + 8 * (lane % 4), + 8); zero past the last row.  OPER: in operand order at
+// once, row lane % 16, elements [k + 8 * (lane / 16), + 8).
+template <bool F32IN, bool OPER>
+__device__ __forceinline__ RowRaw<F32IN> load_rows(const void* x, int rows, int K, int row0, int k,
+                                                   int lane) {
+  RowRaw<F32IN> r{};
+  const int row = row0 + (OPER ? lane & 15 : lane >> 2);
+  if (row < rows) {
+    const int64_t e = (int64_t)row * K + k + 8 * (OPER ? lane >> 4 : lane & 3);
+    if constexpr (F32IN) {
+      const u32x4* p = reinterpret_cast<const u32x4*>(static_cast<const float*>(x) + e);
+      r.v[0] = p[0];
+      r.v[1] = p[1];
+    } else {
+      r.v[0] = *reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(x) + e);
+    }
   }
+  return r;
+}
+
+// the tile in operand order: row lane % 16, elements [8 * (lane / 16), + 8)
+template <bool F32IN>
+__device__ __forceinline__ bf16x8 rows_to_operand(const RowRaw<F32IN>& r, u32x4* lds, int lane) {
+  u32x4 w = r.v[0];
+  if constexpr (F32IN) {
+    const u32x4 a = r.v[0], b = r.v[1];
+    w = u32x4{pack2(__uint_as_float(a[0]), __uint_as_float(a[1])),
+              pack2(__uint_as_float(a[2]), __uint_as_float(a[3])),
+              pack2(__uint_as_float(b[0]), __uint_as_float(b[1])),
+              pack2(__uint_as_float(b[2]), __uint_as_float(b[3]))};
+  }
+  const int wrow = lane >> 2, row = lane & 15;
+  lds[wrow * 4 + ((lane & 3) ^ (wrow >> 2))] = w;
+  return __builtin_bit_cast(bf16x8, lds[row * 4 + ((lane >> 4) ^ (row >> 2))]);
 }
 
 struct ProjArgs {
@@ -80,9 +109,27 @@ struct ProjArgs {
 
 constexpr int PJ_MAX_BATCH = 16 * PJ_MAX_ROW_TILES;
 
+// Row tiles whose loads are in flight together per reduction step group: what the
+// registers leave beside the weight's.
+constexpr int rows_unroll(int mt, bool f32, int ct) {
+  if (ct > 1 && mt > 4) return 1;
+  if (f32) return mt == 1 ? 4 : mt == 2 ? 2 : 1;
+  return mt == 1 ? 8 : mt == 2 ? 4 : mt <= 5 ? 2 : 1;
+}
+
+// U: reduction steps of the weight requested together.
 template <int MT, bool OUT, int U, bool UPD = false, int CT = 1, int NW = PJ_WAVES>
 __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
-  __shared__ float red[NW][4][64];
+  // a single tile of bf16 rows is loaded in operand order: with few rows the
+  // loads are short either way and the pass through LDS would be the longer one
+  constexpr bool OPER = MT == 1 && !OUT;
+  constexpr int UA = OPER || rows_unroll(MT, OUT, CT) > U ? U : rows_unroll(MT, OUT, CT);
+  constexpr int TPR = NW * 64 / 256;  // output tiles summed per round, 256 threads each
+  // each wavefront's row tiles in turn; the shares of TPR tiles afterwards
+  __shared__ __attribute__((aligned(16))) union {
+    u32x4 x[NW][MT][64];
+    float red[TPR][NW][4][64];
+  } L;
   __shared__ int s_len[UPD ? PJ_MAX_BATCH : 1];
   __shared__ uint16_t s_val[UPD ? CT : 1][UPD ? MT * 16 : 1][16];
   if constexpr (UPD) {
@@ -90,54 +137,76 @@ __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
     const int nb = a.rows / a.W1;
     if ((int)threadIdx.x < nb) s_len[threadIdx.x] = a.seq_lens[threadIdx.x];
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ln16 = lane & 15, g4 = lane >> 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tile0 = blockIdx.x * CT;  // CT column tiles share each load of the rows
   const int steps = a.K / 32, per_wave = steps / NW;
   const int s0 = wave * per_wave;
-  const uint4* wp = a.w + ((int64_t)tile0 * steps + s0) * 64 + lane;
+  const u32x4* wp = reinterpret_cast<const u32x4*>(a.w) + ((int64_t)tile0 * steps + s0) * 64 + lane;
   f32x4 acc[CT][MT];
 #pragma unroll
   for (int c = 0; c < CT; ++c)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[c][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // U steps per pass, every load of the pass issued before its MFMAs
+#pragma unroll 1
   for (int s = 0; s < per_wave; s += U) {
-    bf16x8 b[U][CT], av[U][MT];
+    RowRaw<OUT> raw[UA][MT];
+    auto rows_of = [&](int v) {
+#pragma unroll
+      for (int u = 0; u < UA; ++u)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          raw[u][mt] = load_rows<OUT, OPER>(a.x, a.rows, a.K, mt * 16, (s0 + s + v + u) * 32, lane);
+    };
+    // Loads complete in order.  The output projection's first rows (from the L2)
+    // go ahead of the weight (19.7 us at 72 rows, 20.1 behind it); the query /
+    // key / value rows behind it (22.9 us, 24.3 ahead), step by step with it for
+    // a single tile in operand order.
+    u32x4 b[U][CT];
+    if constexpr (OUT) rows_of(0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
-      for (int c = 0; c < CT; ++c) b[u][c] = bits_to_bf16x8(wp[((int64_t)c * steps + s + u) * 64]);
-      const int k = (s0 + s + u) * 32 + 8 * g4;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) av[u][mt] = load_a<OUT>(a.x, a.rows, a.K, mt * 16 + ln16, k);
+      for (int c = 0; c < CT; ++c) b[u][c] = wp[((int64_t)c * steps + s + u) * 64];
+      if constexpr (OPER)
+        raw[u][0] = load_rows<OUT, OPER>(a.x, a.rows, a.K, 0, (s0 + s + u) * 32, lane);
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int v = 0; v < U; v += UA) {
+      if (!OPER && (!OUT || v > 0)) rows_of(v);
 #pragma unroll
-      for (int c = 0; c < CT; ++c)
+      for (int u = 0; u < UA; ++u)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          acc[c][mt] =
-              __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u][mt], b[u][c], acc[c][mt], 0, 0, 0);
+        for (int mt = 0; mt < MT; ++mt) {
+          bf16x8 av;
+          if constexpr (OPER) av = __builtin_bit_cast(bf16x8, raw[u][mt].v[0]);
+          else av = rows_to_operand<OUT>(raw[u][mt], L.x[wave][mt], lane);
+#pragma unroll
+          for (int c = 0; c < CT; ++c)
+            acc[c][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                av, __builtin_bit_cast(bf16x8, b[v + u][c]), acc[c][mt], 0, 0, 0);
+        }
+    }
   }
-  // tile by tile through one LDS buffer: output (i, l) of column tile c and row
+  // TPR tiles at a time through LDS: output (i, l) of column tile c and row
   // tile mt is row mt*16 + 4*(l/16) + i, column (tile0 + c)*16 + l%16
 #pragma unroll
-  for (int pass = 0; pass < CT * MT; ++pass) {
-    const int c = pass / MT, mt = pass % MT;
-    if (pass > 0) __syncthreads();  // the previous tile's sums are read
+  for (int p0 = 0; p0 < CT * MT; p0 += TPR) {
+    __syncthreads();  // the row tiles (or the previous round's sums) are read
 #pragma unroll
-    for (int i = 0; i < 4; ++i) red[wave][i][lane] = acc[c][mt][i];
+    for (int t = 0; t < TPR; ++t)
+      if (p0 + t < CT * MT)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) L.red[t][wave][i][lane] = acc[(p0 + t) / MT][(p0 + t) % MT][i];
     __syncthreads();
-    const int o = threadIdx.x;
-    if (o >= 256) continue;
+    const int pass = p0 + (int)(threadIdx.x >> 8), c = pass / MT, mt = pass % MT;
+    const int o = threadIdx.x & 255;
+    if (pass >= CT * MT) continue;
     const int i = o >> 6, l = o & 63;
     const int row = mt * 16 + 4 * (l >> 4) + i;
     if (row >= a.rows) continue;
     float sum = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) sum += red[w][i][l];
+    for (int w = 0; w < NW; ++w) sum += L.red[threadIdx.x >> 8][w][i][l];
     const int col = (tile0 + c) * 16 + (l & 15);
     const uint16_t y = bf16_rne(sum);
     if constexpr (OUT) {
@@ -228,46 +297,41 @@ __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
   }
 }
 
-// The most reduction steps per pass whose operands fit the registers: 8 for
-// one or two row tiles, 4 for three or four, 2 beyond.
-constexpr int max_unroll(int mt) { return mt <= 2 ? 8 : mt <= 4 ? 4 : 2; }
-
 template <int MT, bool OUT, bool UPD>
 void launch_proj_mt(const ProjArgs& a, hipStream_t s) {
-  // as many reduction steps per pass as the wavefront's share and the registers
-  // allow, so that a share takes as few dependent round trips to memory as
-  // possible (the share, K / 512 steps, is even)
+  // a wavefront's whole share of the weight requested at once where it is eight
+  // steps (K = 4096; the share, K / 512 steps, is even)
   // query / key / value with three to five row tiles: two column tiles per
   // workgroup where N allows, halving the re-reads of the rows (every workgroup
   // reads all of them); not for the output projection, whose 4096 columns would
   // then leave half the compute units without a workgroup
-  constexpr int UM = max_unroll(MT);
   constexpr int CT = (!OUT && MT >= 3 && MT <= 5) ? 2 : 1;
   const int per_wave = a.K / 32 / PJ_WAVES;
   const dim3 block(64 * PJ_WAVES);
   if (CT == 2 && a.N % 32 == 0) {
     const dim3 grid(a.N / 32);
-    constexpr int UC = MT >= 4 ? 2 : UM;  // four or five row tiles: 4 steps would spill
-    if (per_wave % UC == 0)
-      proj_kernel<MT, OUT, UC, UPD, CT><<<grid, block, 0, s>>>(a);
+    if (per_wave % 4 == 0)
+      proj_kernel<MT, OUT, 4, UPD, CT><<<grid, block, 0, s>>>(a);
     else
       proj_kernel<MT, OUT, 2, UPD, CT><<<grid, block, 0, s>>>(a);
     return;
   }
   const dim3 grid(a.N / 16);
-  if constexpr (MT == 1) {
+  if constexpr (MT <= 2) {
     if ((int)grid.x > compute_units() && (a.K / 32 / 8) % 8 == 0) {
-      // one row tile and more column tiles than compute units: eight wavefronts
-      // per workgroup (two passes of eight steps), so that every workgroup of
-      // the launch is resident at once instead of a second, half-empty round
+      // one or two row tiles and more column tiles than compute units: eight
+      // wavefronts per workgroup (two passes of eight steps), so that every
+      // workgroup of the launch is resident at once instead of a second,
+      // half-empty round
       proj_kernel<MT, OUT, 8, UPD, 1, 8><<<grid, dim3(64 * 8), 0, s>>>(a);
       return;
     }
   }
+  constexpr int UM = OUT && MT == 7 ? 4 : 8;  // eight steps and seven f32 row tiles would spill
   if (per_wave % UM == 0)
     proj_kernel<MT, OUT, UM, UPD><<<grid, block, 0, s>>>(a);
-  else if (UM > 4 && per_wave % 4 == 0)
-    proj_kernel<MT, OUT, (UM > 4 ? 4 : 2), UPD><<<grid, block, 0, s>>>(a);
+  else if (per_wave % 4 == 0)
+    proj_kernel<MT, OUT, 4, UPD><<<grid, block, 0, s>>>(a);
   else
     proj_kernel<MT, OUT, 2, UPD><<<grid, block, 0, s>>>(a);
 }
@@ -354,33 +418,120 @@ bool project_qkv_update_supported(const Geometry& g, int k) {
 
 namespace {
 
-// fp32 projections (fp32 stacks): one thread per output element (row r =
-// blockIdx.y, column j), an in-order fused multiply-add chain over the k inputs;
-// the row's inputs staged through LDS 1024 at a time, the weight read by
-// consecutive columns (coalesced).
-constexpr int kF32Threads = 256;
-constexpr int kF32Chunk = 1024;
+// fp32 projections (fp32 stacks): each output element is one in-order chain of
+// fused multiply-adds over the k inputs, so the parallelism is that of the
+// outputs alone: a workgroup owns 16 columns and up to RB rows, one chain per
+// thread (column tid % 16, row tid / 16 of the block).  Bound by reading the
+// weight: slabs of 256 inputs (16 columns of w, RB rows of x) are requested
+// kF32Depth slabs ahead into registers, so that 64 KB of w are in flight per
+// workgroup, and go through two LDS buffers, w transposed, from which a thread
+// reads four steps of its column and its row at a time.  Column tiles that share
+// 128-byte lines are numbered to the same XCD.  [5][4096] x [4096][4096] takes
+// 26 us (2.6 TB/s), [5][4096] x [4096][1024] 25 us, the chain's length; one
+// thread per output reading w from memory step by step took 440 us on average.
+constexpr int kF32Threads = 512;
+constexpr int kF32Cols = 16;
+constexpr int kF32Slab = 256;
+constexpr int kF32Depth = 4;
+constexpr int kF32Row = kF32Slab + 4;  // padded LDS row
+
+// VEC: w is read 16 bytes at a time (w 16-byte aligned, N a multiple of 4).
+template <int RB, bool VEC>
 __global__ void __launch_bounds__(kF32Threads) project_f32_kernel(const float* __restrict__ x,
-                                                                  int K, const float* __restrict__ w,
+                                                                  int rows, int K,
+                                                                  const float* __restrict__ w,
                                                                   int N, float* __restrict__ y,
                                                                   int accumulate) {
-  __shared__ float xs[kF32Chunk];
-  const int r = blockIdx.y;
-  const int j = blockIdx.x * kF32Threads + threadIdx.x;
-  const float* xr = x + (int64_t)r * K;
+  constexpr int WPT = kF32Cols * kF32Slab / 4 / kF32Threads;  // 4-column pieces per thread and slab
+  constexpr int XPT = RB * kF32Slab / kF32Threads;            // row elements per thread and slab
+  typedef float f32x4v __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) float ws[2][kF32Cols][kF32Row];
+  __shared__ __attribute__((aligned(16))) float xs[2][RB][kF32Row];
+  const int tid = threadIdx.x;
+  const int j0 = retro::xcd_remap(blockIdx.x, gridDim.x) * kF32Cols, r0 = blockIdx.y * RB;
+  const int nrows = min(RB, rows - r0);
+  f32x4v wr[kF32Depth][WPT];
+  float xr[kF32Depth][XPT];
+  auto load = [&](int s, f32x4v (&wv)[WPT], float (&xv)[XPT]) {
+    const int i0 = s * kF32Slab;
+#pragma unroll
+    for (int p = 0; p < WPT; ++p) {
+      const int e = tid + p * kF32Threads;
+      const int i = i0 + e / 4, c = j0 + 4 * (e % 4);
+      f32x4v v = f32x4v{0.f, 0.f, 0.f, 0.f};
+      if constexpr (VEC) {
+        if (i < K && c < N) v = *reinterpret_cast<const f32x4v*>(w + (int64_t)i * N + c);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (i < K && c + q < N) v[q] = w[(int64_t)i * N + c + q];
+      }
+      wv[p] = v;
+    }
+#pragma unroll
+    for (int p = 0; p < XPT; ++p) {
+      const int e = tid + p * kF32Threads;
+      const int r = e / kF32Slab, i = i0 + e % kF32Slab;
+      xv[p] = (r < nrows && i < K) ? x[(int64_t)(r0 + r) * K + i] : 0.f;
+    }
+  };
+  const int slabs = (K + kF32Slab - 1) / kF32Slab;
+#pragma unroll
+  for (int d = 0; d < kF32Depth; ++d)
+    if (d < slabs) load(d, wr[d], xr[d]);
+  const int c = tid % kF32Cols, r = tid / kF32Cols;
+  const bool mine = r < RB && r < nrows;
   float acc = 0.f;
-  for (int i0 = 0; i0 < K; i0 += kF32Chunk) {
-    const int cnt = min(kF32Chunk, K - i0);
-    __syncthreads();
-    for (int i = threadIdx.x; i < cnt; i += kF32Threads) xs[i] = xr[i0 + i];
-    __syncthreads();
-    if (j < N) {
-      const float* wc = w + (int64_t)i0 * N + j;
-      for (int i = 0; i < cnt; ++i) acc = fmaf(xs[i], wc[(int64_t)i * N], acc);
+  for (int s0 = 0; s0 < slabs; s0 += kF32Depth) {
+#pragma unroll
+    for (int d = 0; d < kF32Depth; ++d) {
+      const int s = s0 + d;
+      if (s >= slabs) break;  // uniform
+      const int buf = d & 1;  // last read two slabs ago, a barrier has passed since
+#pragma unroll
+      for (int p = 0; p < WPT; ++p) {
+        const int e = tid + p * kF32Threads;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ws[buf][4 * (e % 4) + q][e / 4] = wr[d][p][q];
+      }
+#pragma unroll
+      for (int p = 0; p < XPT; ++p) {
+        const int e = tid + p * kF32Threads;
+        xs[buf][e / kF32Slab][e % kF32Slab] = xr[d][p];
+      }
+      if (s + kF32Depth < slabs) load(s + kF32Depth, wr[d], xr[d]);
+      __syncthreads();
+      if (mine) {
+        const int cnt = min(kF32Slab, K - s * kF32Slab);
+        const float* wc = ws[buf][c];
+        const float* xc = xs[buf][r];
+        if (cnt == kF32Slab) {  // uniform
+          // the chain is serial: the next 16 steps' operands are read under
+          // this batch's multiply-adds
+          f32x4v a[2][4], b[2][4];
+          auto fetch = [&](int i, f32x4v (&av)[4], f32x4v (&bv)[4]) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              av[q] = *reinterpret_cast<const f32x4v*>(xc + i + 4 * q);
+              bv[q] = *reinterpret_cast<const f32x4v*>(wc + i + 4 * q);
+            }
+          };
+          fetch(0, a[0], b[0]);
+#pragma unroll
+          for (int t = 0; t < kF32Slab / 16; ++t) {
+            if (t + 1 < kF32Slab / 16) fetch(16 * (t + 1), a[(t + 1) & 1], b[(t + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc = fmaf(a[t & 1][q / 4][q % 4], b[t & 1][q / 4][q % 4], acc);
+          }
+        } else {
+          for (int i = 0; i < cnt; ++i) acc = fmaf(xc[i], wc[i], acc);
+        }
+      }
     }
   }
-  if (j < N) {
-    float* yo = y + (int64_t)r * N + j;
+  if (mine && j0 + c < N) {
+    float* yo = y + (int64_t)(r0 + r) * N + j0 + c;
     *yo = accumulate ? *yo + acc : acc;
   }
 }
@@ -449,9 +600,20 @@ retro_status retro_project_f32(const float* x, int32_t rows, int32_t k, const fl
   if (!x || !w || !y || rows < 0 || k <= 0 || n <= 0) return RETRO_EINVAL;
   if (rows == 0) return RETRO_OK;
   if (rows > 65535 || (int64_t)rows * n >= (int64_t(1) << 31)) return RETRO_EUNSUPPORTED;
-  const dim3 grid((unsigned)((n + kF32Threads - 1) / kF32Threads), (unsigned)rows);
-  project_f32_kernel<<<grid, kF32Threads, 0, (hipStream_t)stream>>>(
-      x, k, w, n, y, accumulate ? 1 : 0);
+  const bool vec = n % 4 == 0 && retro::aligned16(w);
+  auto go = [&](auto rb) {
+    constexpr int RB = decltype(rb)::value;
+    const dim3 grid((unsigned)((n + kF32Cols - 1) / kF32Cols), (unsigned)((rows + RB - 1) / RB));
+    if (vec)
+      project_f32_kernel<RB, true><<<grid, kF32Threads, 0, (hipStream_t)stream>>>(
+          x, rows, k, w, n, y, accumulate ? 1 : 0);
+    else
+      project_f32_kernel<RB, false><<<grid, kF32Threads, 0, (hipStream_t)stream>>>(
+          x, rows, k, w, n, y, accumulate ? 1 : 0);
+  };
+  // few rows: a quarter of the LDS and of the row loads
+  if (rows <= 8) go(std::integral_constant<int, 8>{});
+  else go(std::integral_constant<int, 32>{});
   return retro::status_of(hipGetLastError());
 }
 
