@@ -421,116 +421,129 @@ namespace {
 // fp32 projections (fp32 stacks): each output element is one in-order chain of
 // fused multiply-adds over the k inputs, so the parallelism is that of the
 // outputs alone: a workgroup owns 16 columns and up to RB rows, one chain per
-// thread (column tid % 16, row tid / 16 of the block).  Bound by reading the
-// weight: slabs of 256 inputs (16 columns of w, RB rows of x) are requested
-// kF32Depth slabs ahead into registers, so that 64 KB of w are in flight per
-// workgroup, and go through two LDS buffers, w transposed, from which a thread
-// reads four steps of its column and its row at a time.  Column tiles that share
-// 128-byte lines are numbered to the same XCD.  [5][4096] x [4096][4096] takes
-// 26 us (2.6 TB/s), [5][4096] x [4096][1024] 25 us, the chain's length; one
-// thread per output reading w from memory step by step took 440 us on average.
-constexpr int kF32Threads = 512;
+// thread of its first wavefronts (column tid % 16, row tid / 16 of the block).
+// Eight more wavefronts feed them: slabs of 256 inputs (16 columns of w, RB rows
+// of x) are requested ahead into registers, w by kF32Depth slabs (64 KB in
+// flight per workgroup), and go through two LDS buffers, w transposed, from
+// which a chain reads four steps of its column and its row at a time, two
+// batches of 16 steps ahead of the multiply-adds.  Column tiles that share
+// 128-byte lines are numbered to the same XCD.  [5][4096] x [4096][4096] takes 24
+// us (2.8 TB/s), [5][4096] x [4096][1024] 21 us, the chain's length, 17 rows 51 us
+// (LDS reads); one thread per output reading w from memory step by step took 430,
+// 315 and 430 us, the same wavefronts feeding and computing 26, 25 and 53 us.
+constexpr int kF32Loaders = 512;
 constexpr int kF32Cols = 16;
 constexpr int kF32Slab = 256;
-constexpr int kF32Depth = 4;
+constexpr int kF32Depth = 4;   // slabs of w in flight
+constexpr int kF32XDepth = 2;  // slabs of x in flight (from the L2)
 constexpr int kF32Row = kF32Slab + 4;  // padded LDS row
 
 // VEC: w is read 16 bytes at a time (w 16-byte aligned, N a multiple of 4).
 template <int RB, bool VEC>
-__global__ void __launch_bounds__(kF32Threads) project_f32_kernel(const float* __restrict__ x,
-                                                                  int rows, int K,
-                                                                  const float* __restrict__ w,
-                                                                  int N, float* __restrict__ y,
-                                                                  int accumulate) {
-  constexpr int WPT = kF32Cols * kF32Slab / 4 / kF32Threads;  // 4-column pieces per thread and slab
-  constexpr int XPT = RB * kF32Slab / kF32Threads;            // row elements per thread and slab
+__global__ void __launch_bounds__(kF32Loaders + RB * kF32Cols) project_f32_kernel(
+    const float* __restrict__ x, int rows, int K, const float* __restrict__ w, int N,
+    float* __restrict__ y, int accumulate) {
+  constexpr int NC = RB * kF32Cols;                           // chain threads
+  constexpr int WPT = kF32Cols * kF32Slab / 4 / kF32Loaders;  // 4-column pieces per loader and slab
+  constexpr int XPT = RB * kF32Slab / kF32Loaders;            // row elements per loader and slab
+  static_assert(NC % 64 == 0 && kF32Depth % 2 == 0 && kF32Depth % kF32XDepth == 0, "slab buffers");
   typedef float f32x4v __attribute__((ext_vector_type(4)));
   __shared__ __attribute__((aligned(16))) float ws[2][kF32Cols][kF32Row];
   __shared__ __attribute__((aligned(16))) float xs[2][RB][kF32Row];
-  const int tid = threadIdx.x;
   const int j0 = retro::xcd_remap(blockIdx.x, gridDim.x) * kF32Cols, r0 = blockIdx.y * RB;
   const int nrows = min(RB, rows - r0);
-  f32x4v wr[kF32Depth][WPT];
-  float xr[kF32Depth][XPT];
-  auto load = [&](int s, f32x4v (&wv)[WPT], float (&xv)[XPT]) {
-    const int i0 = s * kF32Slab;
-#pragma unroll
-    for (int p = 0; p < WPT; ++p) {
-      const int e = tid + p * kF32Threads;
-      const int i = i0 + e / 4, c = j0 + 4 * (e % 4);
-      f32x4v v = f32x4v{0.f, 0.f, 0.f, 0.f};
-      if constexpr (VEC) {
-        if (i < K && c < N) v = *reinterpret_cast<const f32x4v*>(w + (int64_t)i * N + c);
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (i < K && c + q < N) v[q] = w[(int64_t)i * N + c + q];
-      }
-      wv[p] = v;
-    }
-#pragma unroll
-    for (int p = 0; p < XPT; ++p) {
-      const int e = tid + p * kF32Threads;
-      const int r = e / kF32Slab, i = i0 + e % kF32Slab;
-      xv[p] = (r < nrows && i < K) ? x[(int64_t)(r0 + r) * K + i] : 0.f;
-    }
-  };
   const int slabs = (K + kF32Slab - 1) / kF32Slab;
-#pragma unroll
-  for (int d = 0; d < kF32Depth; ++d)
-    if (d < slabs) load(d, wr[d], xr[d]);
-  const int c = tid % kF32Cols, r = tid / kF32Cols;
-  const bool mine = r < RB && r < nrows;
-  float acc = 0.f;
-  for (int s0 = 0; s0 < slabs; s0 += kF32Depth) {
-#pragma unroll
-    for (int d = 0; d < kF32Depth; ++d) {
-      const int s = s0 + d;
-      if (s >= slabs) break;  // uniform
-      const int buf = d & 1;  // last read two slabs ago, a barrier has passed since
+  // Slab s goes through buffer s & 1: written before barrier s, read before
+  // barrier s + 1, and rewritten (slab s + 2) after it.  Every wavefront passes
+  // `slabs` barriers.
+  if ((int)threadIdx.x >= NC) {
+    const int tid = threadIdx.x - NC;
+    f32x4v wr[kF32Depth][WPT];
+    float xr[kF32XDepth][XPT];
+    auto load_w = [&](int s, f32x4v (&wv)[WPT]) {
+      const int i0 = s * kF32Slab;
 #pragma unroll
       for (int p = 0; p < WPT; ++p) {
-        const int e = tid + p * kF32Threads;
+        const int e = tid + p * kF32Loaders;
+        const int i = i0 + e / 4, c = j0 + 4 * (e % 4);
+        f32x4v v = f32x4v{0.f, 0.f, 0.f, 0.f};
+        if constexpr (VEC) {
+          if (i < K && c < N) v = *reinterpret_cast<const f32x4v*>(w + (int64_t)i * N + c);
+        } else {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) ws[buf][4 * (e % 4) + q][e / 4] = wr[d][p][q];
+          for (int q = 0; q < 4; ++q)
+            if (i < K && c + q < N) v[q] = w[(int64_t)i * N + c + q];
+        }
+        wv[p] = v;
       }
+    };
+    auto load_x = [&](int s, float (&xv)[XPT]) {
 #pragma unroll
       for (int p = 0; p < XPT; ++p) {
-        const int e = tid + p * kF32Threads;
-        xs[buf][e / kF32Slab][e % kF32Slab] = xr[d][p];
+        const int e = tid + p * kF32Loaders;
+        const int r = e / kF32Slab, i = s * kF32Slab + e % kF32Slab;
+        xv[p] = (r < nrows && i < K) ? x[(int64_t)(r0 + r) * K + i] : 0.f;
       }
-      if (s + kF32Depth < slabs) load(s + kF32Depth, wr[d], xr[d]);
-      __syncthreads();
-      if (mine) {
-        const int cnt = min(kF32Slab, K - s * kF32Slab);
-        const float* wc = ws[buf][c];
-        const float* xc = xs[buf][r];
-        if (cnt == kF32Slab) {  // uniform
-          // the chain is serial: the next 16 steps' operands are read under
-          // this batch's multiply-adds
-          f32x4v a[2][4], b[2][4];
-          auto fetch = [&](int i, f32x4v (&av)[4], f32x4v (&bv)[4]) {
+    };
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              av[q] = *reinterpret_cast<const f32x4v*>(xc + i + 4 * q);
-              bv[q] = *reinterpret_cast<const f32x4v*>(wc + i + 4 * q);
-            }
-          };
-          fetch(0, a[0], b[0]);
+    for (int d = 0; d < kF32Depth; ++d) {
+      if (d < kF32XDepth && d < slabs) load_x(d, xr[d % kF32XDepth]);
+      if (d < slabs) load_w(d, wr[d]);
+    }
+    for (int s0 = 0; s0 < slabs; s0 += kF32Depth) {
 #pragma unroll
-          for (int t = 0; t < kF32Slab / 16; ++t) {
-            if (t + 1 < kF32Slab / 16) fetch(16 * (t + 1), a[(t + 1) & 1], b[(t + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
+      for (int d = 0; d < kF32Depth; ++d) {
+        const int s = s0 + d;
+        if (s >= slabs) break;  // uniform
+        const int buf = d & 1;
 #pragma unroll
-            for (int q = 0; q < 16; ++q) acc = fmaf(a[t & 1][q / 4][q % 4], b[t & 1][q / 4][q % 4], acc);
-          }
-        } else {
-          for (int i = 0; i < cnt; ++i) acc = fmaf(xc[i], wc[i], acc);
+        for (int p = 0; p < WPT; ++p) {
+          const int e = tid + p * kF32Loaders;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) ws[buf][4 * (e % 4) + q][e / 4] = wr[d][p][q];
         }
+#pragma unroll
+        for (int p = 0; p < XPT; ++p) {
+          const int e = tid + p * kF32Loaders;
+          xs[buf][e / kF32Slab][e % kF32Slab] = xr[d % kF32XDepth][p];
+        }
+        if (s + kF32XDepth < slabs) load_x(s + kF32XDepth, xr[d % kF32XDepth]);
+        if (s + kF32Depth < slabs) load_w(s + kF32Depth, wr[d]);
+        __syncthreads();
       }
     }
+    return;
   }
-  if (mine && j0 + c < N) {
+  const int c = threadIdx.x % kF32Cols, r = threadIdx.x / kF32Cols;
+  float acc = 0.f;
+  for (int s = 0; s < slabs; ++s) {
+    __syncthreads();
+    const int cnt = min(kF32Slab, K - s * kF32Slab);
+    const float* wc = ws[s & 1][c];
+    const float* xc = xs[s & 1][r];
+    if (cnt == kF32Slab) {  // uniform
+      f32x4v a[3][4], b[3][4];
+      auto fetch = [&](int t) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          a[t % 3][q] = *reinterpret_cast<const f32x4v*>(xc + 16 * t + 4 * q);
+          b[t % 3][q] = *reinterpret_cast<const f32x4v*>(wc + 16 * t + 4 * q);
+        }
+      };
+      fetch(0);
+      fetch(1);
+#pragma unroll
+      for (int t = 0; t < kF32Slab / 16; ++t) {
+        if (t + 2 < kF32Slab / 16) fetch(t + 2);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc = fmaf(a[t % 3][q / 4][q % 4], b[t % 3][q / 4][q % 4], acc);
+      }
+    } else {
+      for (int i = 0; i < cnt; ++i) acc = fmaf(xc[i], wc[i], acc);
+    }
+  }
+  if (r < nrows && j0 + c < N) {
     float* yo = y + (int64_t)(r0 + r) * N + j0 + c;
     *yo = accumulate ? *yo + acc : acc;
   }
@@ -605,10 +618,10 @@ retro_status retro_project_f32(const float* x, int32_t rows, int32_t k, const fl
     constexpr int RB = decltype(rb)::value;
     const dim3 grid((unsigned)((n + kF32Cols - 1) / kF32Cols), (unsigned)((rows + RB - 1) / RB));
     if (vec)
-      project_f32_kernel<RB, true><<<grid, kF32Threads, 0, (hipStream_t)stream>>>(
+      project_f32_kernel<RB, true><<<grid, kF32Loaders + RB * kF32Cols, 0, (hipStream_t)stream>>>(
           x, rows, k, w, n, y, accumulate ? 1 : 0);
     else
-      project_f32_kernel<RB, false><<<grid, kF32Threads, 0, (hipStream_t)stream>>>(
+      project_f32_kernel<RB, false><<<grid, kF32Loaders + RB * kF32Cols, 0, (hipStream_t)stream>>>(
           x, rows, k, w, n, y, accumulate ? 1 : 0);
   };
   // few rows: a quarter of the LDS and of the row loads
