@@ -67,8 +67,8 @@ typedef enum {
   /* retro_step: the page scores take a launch of their own even where the
    * scores, selection and attention fit in one launch */
   RETRO_FLAG_SEPARATE_SCORES = 1,
-  /* retro_step: the selection runs at the end of the score launch (implies a
-   * separate score launch) */
+  /* retro_step: the selection follows the scores, ahead of the attention launch
+   * (implies a separate score launch) */
   RETRO_FLAG_SELECT_IN_SCORES = 2,
   /* tests of the failure path only: every bounded wait between the workgroups
    * of a launch gives up after a few polls, as if its producers never came */
@@ -325,8 +325,8 @@ retro_status retro_merge_output_cache(const retro_dims* dims, int32_t step, cons
  * Otherwise, or with RETRO_FLAG_SEPARATE_SCORES, three launches: the scores
  * (with the append), then attention with every attention workgroup selecting
  * in front of it, then combine + merge; with RETRO_FLAG_SELECT_IN_SCORES or
- * for max_pages > 6144, the selection runs at the end of the score launch (or
- * in a launch of its own, above 6144 pages) instead.  Steps
+ * for max_pages > 6144, the selection runs right after the scores, in a launch
+ * of its own, instead.  Steps
  * that keep an earlier selection (top-k reuse, retro_dims.reuse_interval) run
  * the append, Alg. 2 on the kept rows, attention and combine + merge as four
  * launches. */

@@ -108,8 +108,6 @@ retro_status make_geometry(const retro_dims* d, Geometry* g) {
   off += align256(bhs * x.n_splits * x.R * sizeof(float));
   x.ws_err = off;  // sticky error word (a bounded wait ran out, or a foreign geometry)
   off += 256;
-  x.ws_sel = off;  // per-head counters of the score + selection launch
-  off += align256(bhs * kSelCounterInts * (1 + kSelMaxGroups) * sizeof(int32_t));
   x.ws_tok = off;  // per KV head: the step token's page when not kept (selection in attention)
   off += align256(bhs * sizeof(int32_t));
   x.ws_tagged = off;  // the one-launch step's tagged score words, then its key-range words
@@ -285,11 +283,8 @@ retro_status retro_select_pages(const retro_dims* dims, int32_t step, const void
   if (retro::reuse_step(g, step))  // top-k reuse: Alg. 2 on the rows sel holds
     return from_hip(retro::launch_reuse_mask(g, step, *cache, *sel, s));
   float* scores = ws_at(workspace, g.ws_scores);
-  int32_t* counters = reinterpret_cast<int32_t*>((char*)workspace + g.ws_sel);
-  hipError_t e = retro::launch_score(g, step, q_cur, (int64_t)g.hq * g.D, *cache, nullptr, nullptr,
-                                     scores, sel, nullptr, counters, s);
-  if (e == hipSuccess && !retro::score_selects(g))
-    e = retro::launch_topk_mask(g, step, scores, *cache, *sel, nullptr, s);
+  hipError_t e = retro::launch_score(g, q_cur, (int64_t)g.hq * g.D, *cache, nullptr, nullptr, scores, s);
+  if (e == hipSuccess) e = retro::launch_topk_mask(g, step, scores, *cache, *sel, nullptr, s);
   return from_hip(e);
 }
 
@@ -354,6 +349,12 @@ retro_status retro_step_attend_partials(const retro_dims* dims, int32_t step,
                                               (char*)workspace + g.ws_dummy, (hipStream_t)stream));
 }
 
+namespace {
+bool select_in_attention(const Geometry& gp) {
+  return retro::attend_selects(gp) && !(gp.flags & RETRO_FLAG_SELECT_IN_SCORES);
+}
+}  // namespace
+
 retro_status retro_step_launches(const retro_dims* dims, int32_t* launches) {
   Geometry g;
   if (!launches) return RETRO_EINVAL;
@@ -361,11 +362,7 @@ retro_status retro_step_launches(const retro_dims* dims, int32_t* launches) {
   if (st != RETRO_OK) return st;
   Geometry gp = g;
   gp.token_pending = 1;
-  if (one_launch(gp)) {
-    *launches = 1;
-  } else {
-    *launches = retro::score_selects(gp) ? 3 : 4;
-  }
+  *launches = one_launch(gp) ? 1 : select_in_attention(gp) ? 3 : 4;
   return RETRO_OK;
 }
 
@@ -445,11 +442,10 @@ retro_status retro_step(const retro_dims* dims, int32_t step, const void* q_wind
                                               wait_bias(g), ocache, o_out, lse_out, s));
   }
   const Geometry ga = retro::attend_geometry(gp);
-  if (retro::attend_selects(gp) && !(gp.flags & RETRO_FLAG_SELECT_IN_SCORES)) {
+  if (select_in_attention(gp)) {
     // score (+ the token's append) -> attention with the selection in front ->
     // combine + merge (+ last_loaded update, + seq_lens advance)
-    hipError_t e = retro::launch_score(gp, step, q_cur, qbs, *cache, k_new, v_new, scores,
-                                       nullptr, nullptr, nullptr, s);
+    hipError_t e = retro::launch_score(gp, q_cur, qbs, *cache, k_new, v_new, scores, s);
     if (e == hipSuccess)
       e = retro::launch_attend_select(ga, step, q_window, *cache, *sel, scores, o_ws, l_ws, tok,
                                       dummy, s);
@@ -459,13 +455,10 @@ retro_status retro_step(const retro_dims* dims, int32_t step, const void* q_wind
                                       sel->selected, tok);
     return from_hip(e);
   }
-  // score (+ the token's append, + top-k + mask) -> [top-k + mask] -> attention
-  // -> combine + merge (+ seq_lens advance)
-  int32_t* counters = reinterpret_cast<int32_t*>((char*)workspace + g.ws_sel);
-  hipError_t e = retro::launch_score(gp, step, q_cur, qbs, *cache, k_new, v_new, scores, sel, phys,
-                                     counters, s);
-  if (e == hipSuccess && !retro::score_selects(gp))
-    e = retro::launch_topk_mask(gp, step, scores, *cache, *sel, phys, s);
+  // score (+ the token's append) -> top-k + mask -> attention -> combine + merge
+  // (+ seq_lens advance)
+  hipError_t e = retro::launch_score(gp, q_cur, qbs, *cache, k_new, v_new, scores, s);
+  if (e == hipSuccess) e = retro::launch_topk_mask(gp, step, scores, *cache, *sel, phys, s);
   if (e == hipSuccess)
     e = retro::launch_attend(ga, step, q_window, *cache, *sel, phys, o_ws, l_ws, dummy, s);
   if (e == hipSuccess)

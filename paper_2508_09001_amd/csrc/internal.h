@@ -54,11 +54,11 @@ struct Geometry {
   int flags;          // retro_dims.flags (RETRO_FLAG_*)
   int reuse;          // retro_dims.reuse_interval (top-k reuse; < 2: every step selects)
   // workspace layout (bytes): page scores, physical ids of the selection,
-  // split partials, the sticky error word, the score launch's counters, the
+  // split partials, the sticky error word, the
   // step token's page per head, the one-launch step's tagged score words and
   // per-workgroup counter lines, its tagged log-normalisers of the partials and
   // per-head words, a dummy line (never written) for empty loads
-  size_t ws_scores, ws_phys, ws_opart, ws_lpart, ws_err, ws_sel, ws_tok, ws_tagged, ws_heads,
+  size_t ws_scores, ws_phys, ws_opart, ws_lpart, ws_err, ws_tok, ws_tagged, ws_heads,
       ws_lse_tag, ws_head_tag, ws_dummy, ws_total;
   // set for the launches of a step whose token is written by its score launch:
   // seq_lens does not count the token yet (the merge launch advances it), and
@@ -66,10 +66,6 @@ struct Geometry {
   int token_pending;
 };
 
-// counters of the score + selection launch: per KV head 1 + kSelMaxGroups
-// counters, each kSelCounterInts apart (one 128-byte line)
-constexpr int kSelCounterInts = 32;
-constexpr int kSelMaxGroups = 8;
 // polls of a bounded wait (about 0.2 us each) before it gives up
 constexpr int kSpinLimit = 1 << 18;
 // control lines of the one-launch step (its largest grid)
@@ -92,19 +88,15 @@ hipError_t launch_update_kv(const Geometry& g, const retro_kv_cache& c, int n, c
                             const void* v_upd, hipStream_t s);
 // With g.token_pending, the score launch also appends the step's token
 // (k_new, v_new: [batch][h_k][d]) as AppendKV does, without advancing seq_lens.
-// With a selection, counters ([batch * h_k] ints of the workspace, zero
-// between launches) and score_selects(g), it also runs top-k + mask (the last
-// workgroup of each KV head); otherwise launch_topk_mask must follow.
-bool score_selects(const Geometry& g);
-hipError_t launch_score(const Geometry& g, int step, const void* q_cur, int64_t q_batch_stride,
+hipError_t launch_score(const Geometry& g, const void* q_cur, int64_t q_batch_stride,
                         const retro_kv_cache& c, const void* k_new, const void* v_new,
-                        float* scores, const retro_selection* sel, int32_t* sel_phys,
-                        int32_t* counters, hipStream_t s);
+                        float* scores, hipStream_t s);
 // Top-k reuse steps: UpdateAndBuildMask (Alg. 2) on the rows `sel` holds (mask
 // values from last_loaded, then last_loaded = step for the kept pages).
 bool reuse_step(const Geometry& g, int step);
 hipError_t launch_reuse_mask(const Geometry& g, int step, const retro_kv_cache& c,
                              const retro_selection& sel, hipStream_t s);
+// PageSelect + UpdateAndBuildMask from the score launch's page scores.
 hipError_t launch_topk_mask(const Geometry& g, int step, const float* scores,
                             const retro_kv_cache& c, const retro_selection& sel,
                             int32_t* sel_phys, hipStream_t s);

@@ -236,8 +236,7 @@ __device__ __forceinline__ void threshold_select(ThrLds<PER, NW>& L, const uint3
 // and with ta.update last_loaded is set to the step for the kept pages (step - 1
 // for the token's page when it is not kept); else, with ta.tok_out, tok_out[bh]
 // = the token's page if it is not kept, -1 otherwise, for a later launch's
-// update.  Returns the number of kept pages.  The scores are read
-// device-coherently: they may come from other workgroups of the launch.
+// update.  Returns the number of kept pages.
 template <int PER, int NW, typename Kept>
 __device__ __forceinline__ int select_role(const TopkArgs& ta, int bh, int len, int tok_lp,
                                            ThrLds<PER, NW>& L, bool write, Kept&& kept) {
@@ -253,7 +252,7 @@ __device__ __forceinline__ int select_role(const TopkArgs& ta, int bh, int len, 
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int idx = min(j * NTS + tid, last);
-    sv[j] = __hip_atomic_load(srow + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sv[j] = srow[idx];
     a_old[j] = a_row[idx];
     phys[j] = p_row[idx];
   }

@@ -1,7 +1,7 @@
 // PageSelect + UpdateAndBuildMask (Alg. 1, Alg. 2) as a launch of its own, one
-// workgroup per (sequence, KV head), for tables longer than the score and
-// attention launches' own selection takes.  The selection is select_role
-// (threshold.h).
+// workgroup per (sequence, KV head): for retro_select_pages, for tables longer
+// than the attention launch's own selection takes and for
+// RETRO_FLAG_SELECT_IN_SCORES.  The selection is select_role (threshold.h).
 #include "threshold.h"
 
 namespace retro {
@@ -63,8 +63,21 @@ hipError_t launch_topk_mask(const Geometry& g, int step, const float* scores,
   TopkArgs ta{g, step, scores, c.page_table, c.last_loaded, sel.selected, sel.mask,
               sel.num_selected, sel_phys, 1, nullptr};
   const unsigned grid = (unsigned)(g.batch * g.hk);
-  // one workgroup per head: sixteen wavefronts share the pages (at most 16384)
-  topk_mask_kernel<1024, 16><<<grid, 1024, 0, s>>>(ta, c.seq_lens);
+  // one workgroup per head; select_pages at 4 sequences of 4096 pages takes 26.4
+  // us with eight wavefronts of nine pages a thread (28.6 with the selection in
+  // the score launch's last workgroup of each head, 42.7 when that one searched
+  // by 11-bit digits and one scanning wavefront); at 5900 pages eight wavefronts
+  // of twelve take 23.1 us, sixteen of six 22.0
+  if (g.max_pages <= 512)
+    topk_mask_kernel<512, 1><<<grid, 512, 0, s>>>(ta, c.seq_lens);
+  else if (g.max_pages <= 512 * 9)
+    with_select_per(g.max_pages, [&](auto per) {
+      topk_mask_kernel<512, decltype(per)::value><<<grid, 512, 0, s>>>(ta, c.seq_lens);
+    });
+  else if (g.max_pages <= 1024 * 6)
+    topk_mask_kernel<1024, 6><<<grid, 1024, 0, s>>>(ta, c.seq_lens);
+  else
+    topk_mask_kernel<1024, 16><<<grid, 1024, 0, s>>>(ta, c.seq_lens);
   return hipGetLastError();
 }
 

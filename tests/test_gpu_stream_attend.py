@@ -97,7 +97,7 @@ def test_attend_matches_fp64(W, G, P, d):
 
 # table lengths around the stripes of the selection (512 pages each: 2, 5, 9, 12)
 # and past the last one (a launch of its own)
-@pytest.mark.parametrize("mp", [33, 1024, 1025, 2561, 4608, 4700, 6144, 6145])
+@pytest.mark.parametrize("mp", [33, 512, 513, 1024, 1025, 2561, 4608, 4700, 6144, 6145])
 @pytest.mark.parametrize("path", ["select", "step"])
 def test_selection_matches_sorted_scores(mp, path):
     P, B, t = 16, 48 * 16, 9
