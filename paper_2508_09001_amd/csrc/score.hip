@@ -9,15 +9,15 @@
 namespace retro {
 namespace {
 
-// Workgroup shape: eight wavefronts of four pages a pass, up to four passes
-// whose digests are all requested at once (64 KB in flight per workgroup, two
-// workgroups per compute unit).  Bound by reading the digests: 67 MB (8
-// sequences of 32K tokens, 8 KV heads) in 18.5 us, 3.6 TB/s; with a group of 8
-// query heads, whose arithmetic took 19.0 us for 34 MB when every pass read the
-// queries from LDS again, 15.8 us.
+// Workgroup shape: eight wavefronts of four pages a pass, up to two passes whose
+// digests are requested at once (32 KB in flight per workgroup, four workgroups
+// per compute unit).  Bound by reading the digests: 67 MB (8 sequences of 32K
+// tokens, 8 KV heads) in 17.3 us, 3.9 TB/s; 18.5 us with four passes in two
+// workgroups, 17.8 with one.  With a group of 8 query heads, whose arithmetic took
+// 19.0 us for 34 MB when every pass read the queries from LDS again, 13.1 us.
 constexpr int kScoreThreads = 512;
 constexpr int kScoreWaves = kScoreThreads / 64;
-constexpr int kScoreIters = 4;
+constexpr int kScoreIters = 2;
 constexpr int kPassPages = kScoreWaves * 4;              // pages of a pass
 constexpr int kMaxPpb = kPassPages * kScoreIters;        // most pages a workgroup scores
 
@@ -41,7 +41,7 @@ struct TokenArgs {
 };
 
 template <typename T, int D>
-__global__ void __launch_bounds__(kScoreThreads) score_kernel(
+__global__ void __launch_bounds__(kScoreThreads, 8) score_kernel(
     Geometry g, const T* __restrict__ q, int64_t q_bstride, T* __restrict__ dg,
     const int32_t* __restrict__ seq_lens, float* __restrict__ scores, TokenArgs ta, int ppb) {
   // [2][G][D] fp32 queries
