@@ -81,3 +81,40 @@ def test_project_f32_is_the_documented_chain(rows, K, n, off, accumulate):
     B.retro_project_f32(torch.from_numpy(x).cuda(), rows, K, wd, n, y, accumulate=accumulate)
     torch.cuda.synchronize()
     assert np.array_equal(y.cpu().numpy(), want)
+
+
+# runs of 1 token to more than the sequence holds, inside a page and across pages
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("P,d", [(16, 128), (32, 64)])
+@pytest.mark.parametrize("n", [1, 7, 16, 33, 70])
+def test_update_kv_runs(dtype, P, d, n):
+    from paper_2508_09001_amd.layer import RetroLayer
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    hk, mp, lens = 3, 8, [1, 5 * P, 2 * P + 3, 40]
+    lay = RetroLayer(batch=4, num_kv_heads=hk, group=2, head_dim=d, page_size=P, budget=P, window=0,
+                     max_pages=mp, dtype=dtype, page_table=torch.randperm(4 * mp).view(4, mp))
+    g = torch.Generator().manual_seed(n + P)
+
+    def rand(*s):
+        return torch.randn(*s, generator=g).to(td)
+
+    keys, vals = [rand(x, hk, d) for x in lens], [rand(x, hk, d) for x in lens]
+    for s in range(4):
+        lay.prefill(s, keys[s], vals[s])
+    ku, vu = rand(4, n, hk, d), rand(4, n, hk, d)
+    print(f"[update] {dtype} P={P} d={d} n={n}", flush=True)
+    lay.update_kv(ku, vu)
+    torch.cuda.synchronize()
+    table, kc, vc = lay.page_table.cpu().long(), lay.k_cache.cpu(), lay.v_cache.cpu()
+    for s, length in enumerate(lens):
+        m = min(n, length)
+        k = torch.cat([keys[s][:length - m], ku[s, n - m:]])
+        v = torch.cat([vals[s][:length - m], vu[s, n - m:]])
+        pos = torch.arange(length)
+        assert torch.equal(kc[table[s][pos // P], :, pos % P], k)
+        assert torch.equal(vc[table[s][pos // P], :, :, pos % P], v)
+        for p in range(-(-length // P)):
+            dg = lay.digest[s, :, p].cpu()
+            page = k[p * P:(p + 1) * P]
+            assert torch.equal(dg[:, 0], page.amin(0)) and torch.equal(dg[:, 1], page.amax(0))
+    assert lay.seq_lens.tolist() == lens
