@@ -110,13 +110,11 @@ __global__ void __launch_bounds__(kAttendThreads) attend_select_kernel(AttendArg
   const int first = split * g.pages_per_split;
   int seq_len = 0, k = 0;
   auto select = [&] {
-    int tok_lp = -1;
-    seq_len = a.seq_lens[b];
-    if (g.token_pending && token_phys(g, a.pt, b, seq_len) >= 0) {
-      tok_lp = seq_len / g.P;
-      seq_len += 1;
-    }
-    k = select_role(ta, b * g.hk + h, seq_len, tok_lp, *reinterpret_cast<Thr*>(lds), writer,
+    k = select_role(ta, b * g.hk + h,
+                    [&](int& tok_lp) {
+                      return seq_len = select_len(g, a.seq_lens, a.pt, b, tok_lp);
+                    },
+                    *reinterpret_cast<Thr*>(lds), writer,
                     [&](int q, int p, int m, int ph) {
                       if (q >= first && q < first + g.pages_per_split) {
                         l_lp[q - first] = p;

@@ -74,7 +74,10 @@ __global__ void __launch_bounds__(64 * NW) stream_attend_kernel(AttendArgs a, To
   const int tid = thread_index();
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln16 = lane & 15, g4 = lane >> 4;
-  const int wr = wave % NR, wt = wave / NR;  // row tiles wr * RT ..., chunks wt, wt + NT, ...
+  // row tiles wr * RT ..., chunks wt, wt + NT, ...  (Two wavefronts on one chunk
+  // stay together and share its lines in the L1: leaving out a tile without
+  // rows, so that one runs ahead, takes 131K dense from 120 to 159 us.)
+  const int wr = wave % NR, wt = wave / NR;
   // units (sequence, KV head, split, row group), row group fastest: the row
   // groups of a split run at the same time on one XCD and share its L2
   int u = xcd_remap(blockIdx.x, gridDim.x);
@@ -89,7 +92,7 @@ __global__ void __launch_bounds__(64 * NW) stream_attend_kernel(AttendArgs a, To
   // ---- row state: query operands, and the mask value from which row r may
   // not use a page (mask < thr: past query tau uses pages with M_p < tau, the
   // current one every page, a row that does not exist none)
-  bf16x8 q[L_t::kQ ? 1 : RT][KK];
+  bf16x8 q[RT][KK];
   f32x4 acc[RT][DT];
   float m_run[RT], l_run[RT];
   int thr[RT];
@@ -112,11 +115,7 @@ __global__ void __launch_bounds__(64 * NW) stream_attend_kernel(AttendArgs a, To
       if (!live)
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = (__bf16)0.f;
-      if constexpr (L_t::kQ) {
-        if (wt == 0) L.q[wr][j * KK + kk][lane] = v;
-      } else {
-        q[j][kk] = v;
-      }
+      q[j][kk] = v;
     }
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) acc[j][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -125,15 +124,13 @@ __global__ void __launch_bounds__(64 * NW) stream_attend_kernel(AttendArgs a, To
   const int first = split * g.pages_per_split;
   int np, nch;
   if constexpr (PER > 0) {
-    int tok_lp = -1, len = a.seq_lens[b];
-    if (g.token_pending && token_phys(g, a.pt, b, len) >= 0) {
-      tok_lp = len / P;
-      len += 1;
-    }
+    int len = 0;
     // the head's writer: a workgroup of the last split, which has the fewest pages
     const bool writer = split == g.n_splits - 1 && rg == 0;
     const int k = select_role<PER, NW>(
-        ta, bh, len, tok_lp, L.u.thr, writer, [&](int s, int p, int m, int ph) {
+        ta, bh,
+        [&](int& tok_lp) { return len = select_len(g, a.seq_lens, a.pt, b, tok_lp); }, L.u.thr,
+        writer, [&](int s, int p, int m, int ph) {
           if (s >= first && s < first + g.pages_per_split) {
             L.list.phys[s - first] = max(ph, 0);
             L.list.len[s - first] = ph >= 0 ? max(0, min(P, len - p * P)) : 0;
@@ -169,6 +166,13 @@ __global__ void __launch_bounds__(64 * NW) stream_attend_kernel(AttendArgs a, To
       L.list.len[i] = ok ? max(0, min(P, seq_len - lp * P)) : 0;
       L.list.mask[i] = m;
     }
+  }
+  if constexpr (L_t::kQ) {  // only now: waiting for the queries would hold up the selection
+    if (wt == 0)
+#pragma unroll
+      for (int j = 0; j < RT; ++j)
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) L.q[wr][j * KK + kk][lane] = q[j][kk];
   }
   __syncthreads();  // page list ready, the selection's LDS free
 
@@ -254,7 +258,7 @@ __global__ void __launch_bounds__(64 * NW) stream_attend_kernel(AttendArgs a, To
       }
 #pragma unroll
       for (int j = 0; j < RT; ++j) {
-        const bf16x8 qv = L_t::kQ ? ql[qoff + (j * KK + kk) * 64] : q[L_t::kQ ? 0 : j][kk];
+        const bf16x8 qv = L_t::kQ ? ql[qoff + (j * KK + kk) * 64] : q[j][kk];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
           s[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t], qv, s[j][t], 0, 0, 0);

@@ -227,9 +227,10 @@ __device__ __forceinline__ void threshold_select(ThrLds<PER, NW>& L, const uint3
 }
 
 // The selection of KV head bh by a workgroup of NW wavefronts (at most PER * NW
-// * 64 pages).  len: the sequence's tokens, the step's token included when it
-// is stored; tok_lp: that token's logical page (-1: none), for which Alg. 2's
-// current-page rule gives last_loaded = step - 1.  Every kept page goes to
+// * 64 pages).  len_of(tok_lp) gives the sequence's tokens, the step's token
+// included when it is stored, and that token's logical page (-1: none), for which
+// Alg. 2's current-page rule gives last_loaded = step - 1; it is called once the
+// loads that do not depend on it are issued.  Every kept page goes to
 // `kept(slot, page, mask, phys)`: its rank in page order, logical page, mask value
 // M (last_loaded before the step) and physical page (-1: not mapped).  With
 // `write` the selection rows (-1 past the kept pages) and the count are stored,
@@ -237,8 +238,8 @@ __device__ __forceinline__ void threshold_select(ThrLds<PER, NW>& L, const uint3
 // for the token's page when it is not kept); else, with ta.tok_out, tok_out[bh]
 // = the token's page if it is not kept, -1 otherwise, for a later launch's
 // update.  Returns the number of kept pages.
-template <int PER, int NW, typename Kept>
-__device__ __forceinline__ int select_role(const TopkArgs& ta, int bh, int len, int tok_lp,
+template <int PER, int NW, typename LenOf, typename Kept>
+__device__ __forceinline__ int select_role(const TopkArgs& ta, int bh, LenOf&& len_of,
                                            ThrLds<PER, NW>& L, bool write, Kept&& kept) {
   constexpr int NTS = 64 * NW;
   const Geometry& g = ta.g;
@@ -256,6 +257,8 @@ __device__ __forceinline__ int select_role(const TopkArgs& ta, int bh, int len, 
     a_old[j] = a_row[idx];
     phys[j] = p_row[idx];
   }
+  int tok_lp = -1;
+  const int len = len_of(tok_lp);
   thr_clear(L);  // the barrier before the first use is threshold_select's own
   const int n = min((len + g.P - 1) / g.P, g.max_pages);
   const int k = min(min(budget_pages(g, len), n), g.k_max);
@@ -298,6 +301,20 @@ __device__ __forceinline__ int select_role(const TopkArgs& ta, int bh, int len, 
     }
   }
   return k;
+}
+
+// The length of sequence b as select_role takes it: two dependent scalar loads
+// (no launch with a selection writes seq_lens or the page table), whose waits do
+// not wait for the vector loads in flight.
+__device__ __forceinline__ int select_len(const Geometry& g, const int32_t* seq_lens,
+                                          const int32_t* pt, int b, int& tok_lp) {
+  const int pos = sload(seq_lens + b), lp = pos / g.P;
+  tok_lp = -1;
+  if (!g.token_pending || pos < 0 || lp >= g.max_pages) return pos;
+  const int ph = sload(pt + (int64_t)b * g.max_pages + lp);
+  if (ph < 0 || ph >= g.num_phys) return pos;
+  tok_lp = lp;
+  return pos + 1;
 }
 
 // Pages per thread of a 512-thread workgroup's selection, at most, and the

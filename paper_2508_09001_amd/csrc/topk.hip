@@ -12,14 +12,11 @@ __global__ void __launch_bounds__(THREADS) topk_mask_kernel(TopkArgs ta,
                                                             const int32_t* __restrict__ seq_lens) {
   __shared__ __attribute__((aligned(16))) ThrLds<PER, THREADS / 64> L;
   const int bh = blockIdx.x;
-  const int b = bh / ta.g.hk;
   // a pending token (Geometry::token_pending) gets Alg. 2's current-page rule here
-  int tok_lp = -1, len = seq_lens[b];
-  if (ta.g.token_pending && token_phys(ta.g, ta.pt, b, len) >= 0) {
-    tok_lp = len / ta.g.P;
-    len += 1;
-  }
-  select_role<PER, THREADS / 64>(ta, bh, len, tok_lp, L, true, [](int, int, int, int) {});
+  select_role<PER, THREADS / 64>(
+      ta, bh,
+      [&](int& tok_lp) { return select_len(ta.g, seq_lens, ta.pt, bh / ta.g.hk, tok_lp); }, L, true,
+      [](int, int, int, int) {});
 }
 
 // Alg. 2 on the kept selection of a top-k reuse step: one wavefront per
