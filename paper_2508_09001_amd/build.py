@@ -37,10 +37,7 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Werro
 # The one-launch step kernel takes its leading arguments (the pointers of its
 # first loads) preloaded into scalar registers instead of loading them from the
 # kernel-argument segment first.
-# The streamed attention's maxima need no quieting of signalling NaNs (a third of
-# the instructions of its running maximum).
-FILE_FLAGS = {"step_attend.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
-              "stream_attend.hip": ["-fno-honor-nans"]}
+FILE_FLAGS = {"step_attend.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"]}
 
 
 def build(verbose: bool = False) -> str:

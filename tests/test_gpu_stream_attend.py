@@ -95,6 +95,41 @@ def test_attend_matches_fp64(W, G, P, d):
             assert (got_z[fin] - ref_z[fin]).abs().max() <= 1e-5
 
 
+# a NaN key reaches every row that uses its page, and no other row
+@pytest.mark.parametrize("W,G", [(3, 5), (10, 8), (64, 4)])
+def test_nan_key_reaches_the_rows_that_use_it(W, G):
+    P, pages, t, bad = 16, 33, 200, 5
+    lay = _layer(batch=1, group=G, window=W, budget=pages * P, max_pages=pages)
+    g = torch.Generator().manual_seed(W)
+    keys = torch.randn(pages, 2, P, 128, generator=g)
+    vals = torch.randn(pages, 2, P, 128, generator=g).bfloat16()
+    keys[bad, :, 3, 7] = float("nan")
+    lay.k_cache.copy_(keys.bfloat16())
+    lay.v_cache.copy_(vals.transpose(2, 3))
+    lay.seq_lens.fill_(pages * P)
+    lay.num_selected.fill_(pages)
+    lay.selected.copy_(torch.arange(pages, dtype=torch.int32).expand(1, 2, pages))
+    msk = torch.full((1, 2, pages), -1, dtype=torch.int32)
+    msk[:, :, bad] = t - W // 2 - 1          # half of the past rows may use it
+    lay.mask.copy_(msk)
+    q = torch.randn(1, W + 1, 2 * G, 128, generator=g).bfloat16()
+    print(f"[nan] W={W} G={G}", flush=True)
+    lay.attend(t, q.cuda())
+    torch.cuda.synchronize()
+    o = lay.o_part.cpu().double()[0]
+    good = [p for p in range(pages) if p != bad]
+    for r in range(W + 1):
+        if r == W or t - W + r > t - W // 2 - 1:
+            assert torch.isnan(o[r]).all()
+            continue
+        for h in range(2):
+            K = keys[good, h].bfloat16().double().reshape(-1, 128)
+            V = vals[good, h].double().reshape(-1, 128)
+            w = torch.softmax(q[0, r, h * G:(h + 1) * G].double() @ K.t() / math.sqrt(128), 1)
+            bound = 2.0 ** -16 * (w @ V.abs()) + 1e-6   # as above
+            assert ((o[r, h * G:(h + 1) * G] - w @ V).abs() <= bound).all()
+
+
 # table lengths around the stripes of the selection (512 pages each: 2, 5, 9, 12)
 # and past the last one (a launch of its own)
 @pytest.mark.parametrize("mp", [33, 512, 513, 1024, 1025, 2561, 4608, 4700, 6144, 6145])
