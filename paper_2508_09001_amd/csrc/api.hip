@@ -108,6 +108,8 @@ retro_status make_geometry(const retro_dims* d, Geometry* g) {
   off += align256(bhs * x.n_splits * x.R * sizeof(float));
   x.ws_err = off;  // sticky error word (a bounded wait ran out, or a foreign geometry)
   off += 256;
+  x.ws_sel = off;  // per-head counters of the score launch that selects
+  off += align256(bhs * kSelCounterInts * sizeof(int32_t));
   x.ws_tok = off;  // per KV head: the step token's page when not kept (selection in attention)
   off += align256(bhs * sizeof(int32_t));
   x.ws_tagged = off;  // the one-launch step's tagged score words, then its key-range words
@@ -283,7 +285,11 @@ retro_status retro_select_pages(const retro_dims* dims, int32_t step, const void
   if (retro::reuse_step(g, step))  // top-k reuse: Alg. 2 on the rows sel holds
     return from_hip(retro::launch_reuse_mask(g, step, *cache, *sel, s));
   float* scores = ws_at(workspace, g.ws_scores);
-  hipError_t e = retro::launch_score(g, q_cur, (int64_t)g.hq * g.D, *cache, nullptr, nullptr, scores, s);
+  const int64_t qbs = (int64_t)g.hq * g.D;
+  if (retro::score_selects(g))
+    return from_hip(retro::launch_score(g, q_cur, qbs, *cache, nullptr, nullptr, scores, s, step, sel,
+                                        reinterpret_cast<int32_t*>((char*)workspace + g.ws_sel)));
+  hipError_t e = retro::launch_score(g, q_cur, qbs, *cache, nullptr, nullptr, scores, s);
   if (e == hipSuccess) e = retro::launch_topk_mask(g, step, scores, *cache, *sel, nullptr, s);
   return from_hip(e);
 }
@@ -342,7 +348,7 @@ retro_status retro_step_attend_partials(const retro_dims* dims, int32_t step,
                                               wait_limit(g), wait_bias(g), nullptr, nullptr,
                                               nullptr, (hipStream_t)stream));
   }
-  return from_hip(retro::launch_attend_select(retro::attend_geometry(g), step, q_window, *cache,
+  return from_hip(retro::launch_attend_select(retro::attend_geometry(g, true), step, q_window, *cache,
                                               *sel, ws_at(workspace, g.ws_scores),
                                               ws_at(workspace, g.ws_opart),
                                               ws_at(workspace, g.ws_lpart), tok,
@@ -441,7 +447,7 @@ retro_status retro_step(const retro_dims* dims, int32_t step, const void* q_wind
                                               workspace, o_ws, l_ws, tok, err, wait_limit(g),
                                               wait_bias(g), ocache, o_out, lse_out, s));
   }
-  const Geometry ga = retro::attend_geometry(gp);
+  const Geometry ga = retro::attend_geometry(gp, select_in_attention(gp));
   if (select_in_attention(gp)) {
     // score (+ the token's append) -> attention with the selection in front ->
     // combine + merge (+ last_loaded update, + seq_lens advance)

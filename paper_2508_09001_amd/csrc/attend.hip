@@ -189,7 +189,8 @@ hipError_t launch_attend(const Geometry& g, int step, const void* q_window,
                          hipStream_t s) {
   if (!dummy) return hipErrorInvalidValue;
   const AttendArgs a = make_attend_args(g, step, q_window, c, sel, sel_phys, o_ws, l_ws, dummy);
-  if (g.dtype == RETRO_BF16) return launch_stream_attend(a, nullptr, s);
+  if (g.stream) return launch_stream_attend(a, nullptr, s);
+  if (g.dtype == RETRO_BF16) return g.D == 128 ? attend_d<bf16_t, 128>(a, s) : attend_d<bf16_t, 64>(a, s);
   return g.D == 128 ? attend_d<float, 128>(a, s) : attend_d<float, 64>(a, s);
 }
 

@@ -52,13 +52,14 @@ struct Geometry {
   int rtw;            // row tiles per wave
   int waves;          // waves per attention workgroup
   int flags;          // retro_dims.flags (RETRO_FLAG_*)
+  int stream;         // attend_geometry: stream_attend.hip's split and kernel
   int reuse;          // retro_dims.reuse_interval (top-k reuse; < 2: every step selects)
   // workspace layout (bytes): page scores, physical ids of the selection,
-  // split partials, the sticky error word, the
+  // split partials, the sticky error word, the score launch's counters, the
   // step token's page per head, the one-launch step's tagged score words and
   // per-workgroup counter lines, its tagged log-normalisers of the partials and
   // per-head words, a dummy line (never written) for empty loads
-  size_t ws_scores, ws_phys, ws_opart, ws_lpart, ws_err, ws_tok, ws_tagged, ws_heads,
+  size_t ws_scores, ws_phys, ws_opart, ws_lpart, ws_err, ws_sel, ws_tok, ws_tagged, ws_heads,
       ws_lse_tag, ws_head_tag, ws_dummy, ws_total;
   // set for the launches of a step whose token is written by its score launch:
   // seq_lens does not count the token yet (the merge launch advances it), and
@@ -66,6 +67,8 @@ struct Geometry {
   int token_pending;
 };
 
+// counters of the score launch that selects: one per KV head, a 128-byte line apart
+constexpr int kSelCounterInts = 32;
 // polls of a bounded wait (about 0.2 us each) before it gives up
 constexpr int kSpinLimit = 1 << 18;
 // control lines of the one-launch step (its largest grid)
@@ -88,9 +91,14 @@ hipError_t launch_update_kv(const Geometry& g, const retro_kv_cache& c, int n, c
                             const void* v_upd, hipStream_t s);
 // With g.token_pending, the score launch also appends the step's token
 // (k_new, v_new: [batch][h_k][d]) as AppendKV does, without advancing seq_lens.
+// With `sel` (score_selects(g) only) it also runs PageSelect + UpdateAndBuildMask;
+// counters: [batch * h_k * kSelCounterInts] ints of the workspace, zero between
+// launches.
+bool score_selects(const Geometry& g);
 hipError_t launch_score(const Geometry& g, const void* q_cur, int64_t q_batch_stride,
                         const retro_kv_cache& c, const void* k_new, const void* v_new,
-                        float* scores, hipStream_t s);
+                        float* scores, hipStream_t s, int step = 0,
+                        const retro_selection* sel = nullptr, int32_t* counters = nullptr);
 // Top-k reuse steps: UpdateAndBuildMask (Alg. 2) on the rows `sel` holds (mask
 // values from last_loaded, then last_loaded = step for the kept pages).
 bool reuse_step(const Geometry& g, int step);
@@ -106,8 +114,9 @@ hipError_t launch_attend(const Geometry& g, int step, const void* q_window,
                          hipStream_t s);
 // The attention of the multi-launch plans for bf16 layers (stream_attend.hip) has
 // a split of its own: attend_geometry(g) is g with that split (g itself for
-// fp32), to be used for launch_attend and the combine of its partials.
-Geometry attend_geometry(const Geometry& g);
+// fp32 and where attend_kernel is the faster one), to be used for launch_attend and the combine of its partials.
+// `selects`: for launch_attend_select.
+Geometry attend_geometry(const Geometry& g, bool selects = false);
 // Attention with the page selection (top-k + Alg. 2's mask) made by each of its
 // workgroups from the score launch's page scores (attend_selects(g); g from
 // attend_geometry); writes the selection outputs (rows, mask, count) but not

@@ -2,9 +2,15 @@
 // the fixed fp32 order described in roles.h (score_role).  Digests are stored
 // per logical page, so a KV head's digests form one contiguous stream; a
 // workgroup scores a block of consecutive pages, four per wavefront.
+//
+// With PER > 0 the last workgroup of each KV head to finish also makes the head's
+// selection (select_role, threshold.h), for retro_select_pages on small tables
+// (score_selects).  Scores are then written and read device-coherently, past the
+// XCDs' L2s, and a workgroup counts itself out only after its score stores have
+// completed, so that the last one reads them all.
 #include <algorithm>
 
-#include "roles.h"
+#include "threshold.h"
 
 namespace retro {
 namespace {
@@ -40,11 +46,17 @@ struct TokenArgs {
   const int32_t* pt;
 };
 
-template <typename T, int D>
-__global__ void __launch_bounds__(kScoreThreads, 8) score_kernel(
+struct SelectArgs {
+  TopkArgs tk;
+  int32_t* count;  // one counter per KV head, kSelCounterInts apart, zero between launches
+};
+
+template <typename T, int D, int PER>
+__global__ void __launch_bounds__(kScoreThreads, PER ? 4 : 8) score_kernel(
     Geometry g, const T* __restrict__ q, int64_t q_bstride, T* __restrict__ dg,
-    const int32_t* __restrict__ seq_lens, float* __restrict__ scores, TokenArgs ta, int ppb) {
-  // [2][G][D] fp32 queries
+    const int32_t* __restrict__ seq_lens, float* __restrict__ scores, TokenArgs ta, SelectArgs sa,
+    int ppb) {
+  // [2][G][D] fp32 queries while scoring; the selection's histograms after
   extern __shared__ __attribute__((aligned(16))) float dyn_lds[];
   static_assert(ScoreShape<T, D>::PPW == 4, "four pages per wavefront and pass");
   const int page0 = blockIdx.x * ppb, page_end = min(page0 + ppb, g.max_pages);
@@ -53,7 +65,9 @@ __global__ void __launch_bounds__(kScoreThreads, 8) score_kernel(
   // A workgroup whose pages all lie past the sequence (the step's token
   // included) has nothing to score: with sequences of mixed lengths the grid,
   // sized for the longest, would otherwise load their stale digests.
-  if (page0 * g.P > sload(seq_lens + b)) return;  // uniform
+  // (The first one always stays: pos0 >= 0.)
+  const int pos0 = max(sload(seq_lens + b), 0);
+  if (page0 * g.P > pos0) return;  // uniform
   // the step's token and the sequence's pages (after the digest loads are issued)
   auto tok_of = [&](int& np) {
     const int pos = seq_lens[b];
@@ -73,21 +87,58 @@ __global__ void __launch_bounds__(kScoreThreads, 8) score_kernel(
   score_role<T, D, kScoreIters, false, 0, kScoreThreads>(
       g, page0, page_end, q + b * q_bstride + (int64_t)h * g.G * D, dg + bh * g.max_pages * 2 * D,
       dyn_lds, tok_of, [] {},
-      [&](int page, float v) { srow[page] = v; });
+      [&](int page, float v) {
+        if constexpr (PER > 0)
+          __hip_atomic_store(srow + page, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+          srow[page] = v;
+      });
+  if constexpr (PER > 0) {
+    __shared__ int s_last;
+    __builtin_amdgcn_s_waitcnt(0);  // this wavefront's score stores have completed
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      // workgroups of the head that score (the others have returned)
+      const int active = min((int)gridDim.x, pos0 / (g.P * ppb) + 1);
+      int32_t* n = sa.count + bh * kSelCounterInts;
+      const bool last =
+          __hip_atomic_fetch_add(n, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == active - 1;
+      if (last) __hip_atomic_store(n, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_last = last;
+    }
+    __syncthreads();
+    if (s_last)
+      select_role<PER, kScoreWaves, true>(
+          sa.tk, (int)bh, [&](int& tok_lp) { return select_len(g, seq_lens, ta.pt, b, tok_lp); },
+          *reinterpret_cast<ThrLds<PER, kScoreWaves>*>(dyn_lds), true, [](int, int, int, int) {});
+  }
 }
 
-template <typename T, int D>
+template <typename T, int D, int PER>
 hipError_t score_t(const Geometry& g, const void* q, int64_t qbs, const retro_kv_cache& c,
-                   const void* k_new, const void* v_new, float* scores, hipStream_t s) {
+                   const void* k_new, const void* v_new, float* scores, const SelectArgs& sa,
+                   hipStream_t s) {
   int nbh, ppb;
   score_split(g, &nbh, &ppb);
   if (ppb < 1 || ppb > kMaxPpb || nbh < 1) return hipErrorInvalidValue;
   dim3 grid(nbh, g.hk, g.batch);
-  const size_t lds = sizeof(float) * 2 * g.G * D;  // the queries' q+ and q- halves
+  size_t lds = sizeof(float) * 2 * g.G * D;  // the queries' q+ and q- halves
+  if constexpr (PER > 0) lds = std::max(lds, sizeof(ThrLds<PER, kScoreWaves>));
   const TokenArgs ta{k_new, v_new, c.k_cache, c.v_cache, c.page_table};
-  score_kernel<T, D><<<grid, kScoreThreads, lds, s>>>(g, (const T*)q, qbs, (T*)c.digest,
-                                                     c.seq_lens, scores, ta, ppb);
+  score_kernel<T, D, PER><<<grid, kScoreThreads, lds, s>>>(g, (const T*)q, qbs, (T*)c.digest,
+                                                          c.seq_lens, scores, ta, sa, ppb);
   return hipGetLastError();
+}
+
+template <typename T, int D>
+hipError_t score_d(const Geometry& g, const void* q, int64_t qbs, const retro_kv_cache& c,
+                   const void* k_new, const void* v_new, float* scores, const SelectArgs& sa,
+                   hipStream_t s) {
+  auto go = [&](auto per) {
+    return score_t<T, D, decltype(per)::value>(g, q, qbs, c, k_new, v_new, scores, sa, s);
+  };
+  if (!sa.count) return go(std::integral_constant<int, 0>{});
+  return with_select_per(g.max_pages, go);
 }
 
 }  // namespace
@@ -105,14 +156,30 @@ int compute_units() {
   return cus[dev];
 }
 
+// Up to here a call's host time, a launch fewer, is what the last workgroup's
+// selection saves; from about twice as many pages the chain from a head's last
+// score to its rows costs more (16K pages of 16 heads 10.3 against 11.6 us, 33K
+// pages 16.0 against 13.8, 131K pages 41 against 28).
+bool score_selects(const Geometry& g) {
+  return (int64_t)g.batch * g.hk * g.max_pages <= 1 << 15 && g.max_pages <= kScoreThreads * kSelectPer;
+}
+
 hipError_t launch_score(const Geometry& g, const void* q_cur, int64_t q_batch_stride,
                         const retro_kv_cache& c, const void* k_new, const void* v_new,
-                        float* scores, hipStream_t s) {
+                        float* scores, hipStream_t s, int step, const retro_selection* sel,
+                        int32_t* counters) {
+  SelectArgs sa{};
+  if (sel) {
+    if (!counters || !score_selects(g)) return hipErrorInvalidValue;
+    sa.tk = TopkArgs{g, step, scores, c.page_table, c.last_loaded, sel->selected, sel->mask,
+                     sel->num_selected, nullptr, 1, nullptr};
+    sa.count = counters;
+  }
   if (g.dtype == RETRO_BF16)
-    return g.D == 128 ? score_t<bf16_t, 128>(g, q_cur, q_batch_stride, c, k_new, v_new, scores, s)
-                      : score_t<bf16_t, 64>(g, q_cur, q_batch_stride, c, k_new, v_new, scores, s);
-  return g.D == 128 ? score_t<float, 128>(g, q_cur, q_batch_stride, c, k_new, v_new, scores, s)
-                    : score_t<float, 64>(g, q_cur, q_batch_stride, c, k_new, v_new, scores, s);
+    return g.D == 128 ? score_d<bf16_t, 128>(g, q_cur, q_batch_stride, c, k_new, v_new, scores, sa, s)
+                      : score_d<bf16_t, 64>(g, q_cur, q_batch_stride, c, k_new, v_new, scores, sa, s);
+  return g.D == 128 ? score_d<float, 128>(g, q_cur, q_batch_stride, c, k_new, v_new, scores, sa, s)
+                    : score_d<float, 64>(g, q_cur, q_batch_stride, c, k_new, v_new, scores, sa, s);
 }
 
 }  // namespace retro

@@ -29,6 +29,8 @@
 // by HBM.  Batch 4, 256 pages, 264 rows (67 MB) 75 -> 55 us; 131K tokens, 256 pages
 // of 32, 260 rows (34 MB) 45 -> 27 us: bound by vector instructions (38 % of the
 // cycles the matrix cores are busy, 54 % the vector units).
+#include <algorithm>
+
 #include "threshold.h"
 
 namespace retro {
@@ -413,26 +415,50 @@ hipError_t go_d(const AttendArgs& a, const TopkArgs* ta, hipStream_t s) {
 
 }  // namespace
 
-Geometry attend_geometry(const Geometry& g) {
+namespace {
+// Without a selection in front, splits of a few chunks go to attend_kernel: a
+// wavefront's merge of several row tiles here is long straight-line code that
+// runs once.  g: attend_kernel's split, x: the row tiles here.  Attention and
+// combine, 8 KV heads, attend_kernel / here in us: 36 rows, 8 pages 8.4 / 12.8, 128
+// pages (two chunks a split) 12.6 / 15.8, 256 pages (four) 15.5 / 17.0, 512 pages
+// (eight) 22.4 / 20.4; 68 rows, 128 pages 14.8 / 16.7, 512 pages 26.6 / 23.0.  136
+// rows (two tiles a wavefront there), 32 pages 14.0 / 15.7 with half the compute
+// units, 64 pages 17.7 / 16.3 with all; 100 rows (two tiles a wavefront here), 8
+// pages 9.8 / 11.4 with an eighth, 32 pages 12.9 / 12.5 with half.  One tile a
+// wavefront here: 7.8 / 7.5 to 20.5 / 13.8, never there.
+bool attend_kernel_wins(const Geometry& g, const Geometry& x) {
+  const int cap = compute_units();
+  const int64_t wgs = (int64_t)g.batch * g.hk * g.n_rgroups * g.n_splits;
+  if (wgs > cap || x.tiles_per_group == 1) return false;
+  const bool three = x.tiles_per_group == 3 || x.tiles_per_group > 4;  // tiles a wavefront (go_d)
+  if (three && g.rtw == 1) return g.chunks_per_split <= 4;
+  return g.chunks_per_split == 1 && wgs <= (three ? cap / 2 : cap / 4);
+}
+}  // namespace
+
+Geometry attend_geometry(const Geometry& g, bool selects) {
   if (g.dtype != RETRO_BF16) return g;
   Geometry x = g;
   constexpr int kMaxTiles = 6;  // two wavefronts side by side, three tiles each
   x.n_rgroups = (g.row_tiles + kMaxTiles - 1) / kMaxTiles;
   x.tiles_per_group = (g.row_tiles + x.n_rgroups - 1) / x.n_rgroups;
   const int nw = x.tiles_per_group <= 3 ? NW : NW / 2;  // wavefronts over the chunks (go_d)
+  if (!selects && attend_kernel_wins(g, x)) return g;
+  x.stream = 1;
   // One workgroup per compute unit (its registers); the split count with the
   // smallest time, counted in chunk iterations of a wavefront: rounds of
   // workgroups times the iterations of one, plus three for its start and merge.
+  // (For a number of iterations, the fewest splits that reach it.)
   const int64_t heads = (int64_t)g.batch * g.hk * x.n_rgroups;
   const int cap = compute_units();
+  const int cps_max = kListPages / g.chunk_pages;
   int best = 0;
-  double best_cost = 0;
-  for (int ns = 1; ns <= g.n_splits; ++ns) {
-    const int cps = (g.chunks_max + ns - 1) / ns;
-    if (cps * g.chunk_pages > kListPages) continue;
-    if ((g.chunks_max + cps - 1) / cps != ns) continue;
-    const int64_t rounds = (heads * ns + cap - 1) / cap;
-    const double cost = (double)rounds * ((cps + nw - 1) / nw + 3);
+  int64_t best_cost = 0;
+  for (int it = (std::min(g.chunks_max, cps_max) + nw - 1) / nw; it >= 1; --it) {
+    const int cps = std::min(it * nw, cps_max);
+    const int ns = (g.chunks_max + cps - 1) / cps;
+    if (ns > g.n_splits) break;
+    const int64_t cost = (heads * ns + cap - 1) / cap * (it + 3);
     if (best == 0 || cost < best_cost) {
       best = ns;
       best_cost = cost;

@@ -237,8 +237,9 @@ __device__ __forceinline__ void threshold_select(ThrLds<PER, NW>& L, const uint3
 // and with ta.update last_loaded is set to the step for the kept pages (step - 1
 // for the token's page when it is not kept); else, with ta.tok_out, tok_out[bh]
 // = the token's page if it is not kept, -1 otherwise, for a later launch's
-// update.  Returns the number of kept pages.
-template <int PER, int NW, typename LenOf, typename Kept>
+// update.  COH: the scores come from other workgroups of the same launch and are
+// read device-coherently.  Returns the number of kept pages.
+template <int PER, int NW, bool COH = false, typename LenOf, typename Kept>
 __device__ __forceinline__ int select_role(const TopkArgs& ta, int bh, LenOf&& len_of,
                                            ThrLds<PER, NW>& L, bool write, Kept&& kept) {
   constexpr int NTS = 64 * NW;
@@ -253,7 +254,10 @@ __device__ __forceinline__ int select_role(const TopkArgs& ta, int bh, LenOf&& l
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int idx = min(j * NTS + tid, last);
-    sv[j] = srow[idx];
+    if constexpr (COH)
+      sv[j] = __hip_atomic_load(srow + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+      sv[j] = srow[idx];
     a_old[j] = a_row[idx];
     phys[j] = p_row[idx];
   }
