@@ -117,8 +117,9 @@ constexpr int rows_unroll(int mt, bool f32, int ct) {
   return mt == 1 ? 8 : mt == 2 ? 4 : mt <= 5 ? 2 : 1;
 }
 
-// U: reduction steps of the weight requested together.
-template <int MT, bool OUT, int U, bool UPD = false, int CT = 1, int NW = PJ_WAVES>
+// U: reduction steps of the weight requested together.  SH: shares of the reduction
+// per wavefront, each summed up by itself and added to the others in LDS in order.
+template <int MT, bool OUT, int U, bool UPD = false, int CT = 1, int NW = PJ_WAVES, int SH = 1>
 __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
   // a single tile of bf16 rows is loaded in operand order: with few rows the
   // loads are short either way and the pass through LDS would be the longer one
@@ -128,7 +129,7 @@ __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
   // each wavefront's row tiles in turn; the shares of TPR tiles afterwards
   __shared__ __attribute__((aligned(16))) union {
     u32x4 x[NW][MT][64];
-    float red[TPR][NW][4][64];
+    float red[TPR][NW * SH][4][64];
   } L;
   __shared__ int s_len[UPD ? PJ_MAX_BATCH : 1];
   __shared__ uint16_t s_val[UPD ? CT : 1][UPD ? MT * 16 : 1][16];
@@ -139,16 +140,11 @@ __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
   }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tile0 = blockIdx.x * CT;  // CT column tiles share each load of the rows
-  const int steps = a.K / 32, per_wave = steps / NW;
-  const int s0 = wave * per_wave;
+  const int steps = a.K / 32, per_share = steps / (NW * SH);
+  const int s0 = wave * SH * per_share;
   const u32x4* wp = reinterpret_cast<const u32x4*>(a.w) + ((int64_t)tile0 * steps + s0) * 64 + lane;
-  f32x4 acc[CT][MT];
-#pragma unroll
-  for (int c = 0; c < CT; ++c)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[c][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-  for (int s = 0; s < per_wave; s += U) {
+  f32x4 acc[SH][CT][MT];
+  auto one_pass = [&](int s, f32x4 (&acc)[CT][MT]) {
     RowRaw<OUT> raw[UA][MT];
     auto rows_of = [&](int v) {
 #pragma unroll
@@ -186,6 +182,15 @@ __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
                 av, __builtin_bit_cast(bf16x8, b[v + u][c]), acc[c][mt], 0, 0, 0);
         }
     }
+  };
+#pragma unroll
+  for (int sh = 0; sh < SH; ++sh) {
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[sh][c][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int s = 0; s < per_share; s += U) one_pass(sh * per_share + s, acc[sh]);
   }
   // TPR tiles at a time through LDS: output (i, l) of column tile c and row
   // tile mt is row mt*16 + 4*(l/16) + i, column (tile0 + c)*16 + l%16
@@ -196,7 +201,10 @@ __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
     for (int t = 0; t < TPR; ++t)
       if (p0 + t < CT * MT)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) L.red[t][wave][i][lane] = acc[(p0 + t) / MT][(p0 + t) % MT][i];
+        for (int sh = 0; sh < SH; ++sh)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            L.red[t][wave * SH + sh][i][lane] = acc[sh][(p0 + t) / MT][(p0 + t) % MT][i];
     __syncthreads();
     const int pass = p0 + (int)(threadIdx.x >> 8), c = pass / MT, mt = pass % MT;
     const int o = threadIdx.x & 255;
@@ -206,7 +214,7 @@ __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
     if (row >= a.rows) continue;
     float sum = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) sum += L.red[threadIdx.x >> 8][w][i][l];
+    for (int w = 0; w < NW * SH; ++w) sum += L.red[threadIdx.x >> 8][w][i][l];
     const int col = (tile0 + c) * 16 + (l & 15);
     const uint16_t y = bf16_rne(sum);
     if constexpr (OUT) {
@@ -318,12 +326,14 @@ void launch_proj_mt(const ProjArgs& a, hipStream_t s) {
   }
   const dim3 grid(a.N / 16);
   if constexpr (MT <= 2) {
-    if ((int)grid.x > compute_units() && (a.K / 32 / 8) % 8 == 0) {
-      // one or two row tiles and more column tiles than compute units: eight
-      // wavefronts per workgroup (two passes of eight steps), so that every
-      // workgroup of the launch is resident at once instead of a second,
-      // half-empty round
-      proj_kernel<MT, OUT, 8, UPD, 1, 8><<<grid, dim3(64 * 8), 0, s>>>(a);
+    // one or two row tiles and more column tiles than compute units: eight
+    // wavefronts per workgroup (two passes of eight steps), so that every
+    // workgroup of the launch is resident at once instead of a second,
+    // half-empty round.  Two tiles keep the sixteen shares of the other shapes:
+    // the sums are formed in the same order whatever N is.
+    constexpr int SH = MT == 2 ? 2 : 1;
+    if ((int)grid.x > compute_units() && (a.K / 32 / (8 * SH)) % 8 == 0) {
+      proj_kernel<MT, OUT, 8, UPD, 1, 8, SH><<<grid, dim3(64 * 8), 0, s>>>(a);
       return;
     }
   }

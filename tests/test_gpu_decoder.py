@@ -210,6 +210,36 @@ def test_project_qkv_matches_fp64_products(rows, K, nq, nkv):
     assert np.mean(got == ref_b) > 0.98
 
 
+# 17 to 32 rows: a column's sums are formed in the same order whether the launch has
+# more column tiles than compute units (eight wavefronts of two shares each) or not
+@pytest.mark.parametrize("rows,K", [(17, 4096), (32, 4096), (20, 2048), (24, 8192)])
+def test_projections_do_not_depend_on_the_number_of_columns(rows, K):
+    import torch
+    from paper_2508_09001_amd import binding as B
+    n, part = 6144, 1536
+    g = torch.Generator().manual_seed(rows + K)
+    x = torch.randn(rows, K, generator=g).bfloat16().cuda()
+    wp = torch.empty(K, n, dtype=torch.bfloat16, device="cuda")
+    B.retro_pack_weight((torch.randn(K, n, generator=g) * K ** -0.5).bfloat16().cuda(), K, n, wp)
+    print(f"[proj] columns rows={rows} K={K}", flush=True)
+
+    def project(w, cols):
+        q = torch.empty(rows, cols - 32, dtype=torch.bfloat16, device="cuda")
+        k, v = (torch.empty(rows, 16, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        B.retro_project_qkv(x, rows, K, w, cols - 32, 16, q, k, v)
+        h, xn = torch.zeros(rows, cols, device="cuda"), torch.empty(rows, cols, device="cuda").bfloat16()
+        B.retro_project_out(x.float(), rows, K, w, cols, h, xn)
+        torch.cuda.synchronize()
+        return torch.cat([q, k, v], 1), h
+
+    whole = project(wp, n)
+    tiles = wp.view(n // 16, -1)          # a packed weight's column tiles are contiguous
+    for c in range(0, n, part):
+        some = project(tiles[c // 16:(c + part) // 16], part)
+        for a, b in zip(whole, some):
+            assert torch.equal(a[:, c:c + part], b)
+
+
 @pytest.mark.parametrize("rows,K,n", [(1, 1024, 512), (17, 4096, 4096), (40, 2048, 256),
                                       (18, 1024, 48), (72, 4096, 1024), (100, 1024, 256)])
 def test_project_out_adds_the_residual(rows, K, n):
