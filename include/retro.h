@@ -248,7 +248,11 @@ retro_status retro_select_pages(const retro_dims* dims, int32_t step, const void
  * and (r == W or mask[p] < tau); every stored token of a used page counts.
  * Output per row and query head: o_part [batch][W+1][h_q][d] fp32 (softmax-weighted
  * values) and lse_part [batch][W+1][h_q] fp32 = ln sum exp(sm_scale * q.k);
- * an empty set gives (0, -inf).  Reads only; writes o_part, lse_part, workspace. */
+ * an empty set gives (0, -inf).  A NaN score, or one of +inf, makes its row's
+ * outputs and log-normaliser NaN (also through retro_step and
+ * retro_merge_output_cache).  A NaN or infinite value of a selected page can reach
+ * every row of its KV head, also rows that do not use the page: a zero weight
+ * times it is NaN.  Reads only; writes o_part, lse_part, workspace. */
 retro_status retro_decode_attend(const retro_dims* dims, int32_t step, const void* q_window,
                                  const retro_kv_cache* cache, const retro_selection* sel,
                                  float* o_part, float* lse_part, void* workspace,

@@ -1030,7 +1030,9 @@ __device__ __forceinline__ void attend_role(const AttendArgs& a, int b, int h, i
     if (rho < g.R) {
       const float inv = l > 0.f ? 1.f / l : 0.f;
       float* orow = a.o_ws + (part + rho) * D;
-      const float lse = l > 0.f ? (m_run[j] + __log2f(l)) * kLn2 : -INFINITY;
+      // -inf for an empty sum; +inf (fminf skips NaN) for a NaN one, from NaN or
+      // infinite scores: the combine then makes the row NaN
+      const float lse = fminf((m_run[j] + __log2f(l)) * kLn2, INFINITY);
 #pragma unroll
       for (int dt = 0; dt < D / 16; ++dt) {
         const f32x4 o = acc[j][dt] * inv;
@@ -1104,7 +1106,8 @@ struct Row {
 // Z = ln sum_s e^{Z_s}.  Splits are taken GS at a time with every load of the
 // group (log-normalisers one per lane, output rows E floats per lane) in
 // flight together; groups after the first are folded in relative to the
-// running maximum.
+// running maximum.  (A split with a NaN sum has the log-normaliser +inf, whose
+// weight, exp(inf - inf), makes the row and its normaliser NaN.)
 // COH: the partials and the selection count come from other workgroups of the
 // same launch: device-coherent loads.  ZPRE: the log-normalisers are not loaded
 // here: lane s of zl.z[r] holds split s's for row r (at most 64 splits).
@@ -1203,18 +1206,14 @@ __device__ __forceinline__ void combine_splits(const MergeArgs& a, int bh, const
 template <int D>
 __device__ __forceinline__ Row<D> lse_merge(const Row<D>& x, const Row<D>& y) {
   Row<D> r;
-  const float m = fmaxf(x.z, y.z);
-  if (m == -INFINITY) {
-#pragma unroll
-    for (int e = 0; e < Row<D>::E; ++e) r.o[e] = 0.f;
-    r.z = -INFINITY;
-    return r;
-  }
-  const float wa = __expf(x.z - m), wb = __expf(y.z - m);
-  const float inv = 1.f / (wa + wb);
+  // without a branch: two empty sides give a sum of 0, a NaN normaliser (which
+  // fmaxf skips) a NaN row
+  const float mx = fmaxf(x.z, y.z), m = mx == -INFINITY ? 0.f : mx;
+  const float wa = __expf(x.z - m), wb = __expf(y.z - m), sum = wa + wb;
+  const float inv = sum == 0.f ? 0.f : 1.f / sum;
 #pragma unroll
   for (int e = 0; e < Row<D>::E; ++e) r.o[e] = (wa * x.o[e] + wb * y.o[e]) * inv;
-  r.z = m + __logf(wa + wb);
+  r.z = m + __logf(sum);
   return r;
 }
 

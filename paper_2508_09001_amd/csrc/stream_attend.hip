@@ -357,8 +357,10 @@ __global__ void __launch_bounds__(64 * NW) stream_attend_kernel(AttendArgs a, To
     for (int w = 0; w < NT; ++w)
       sum += L.l[w * NR + wr][rr] * __builtin_amdgcn_exp2f(L.m[w * NR + wr][rr] - Mu);
     const float f = sum > 0.f ? __builtin_amdgcn_exp2f(m_run[j] - Mu) / sum : 0.f;
+    // -inf for an empty sum; +inf (fminf skips NaN) for a NaN one, from NaN or
+    // infinite scores: the combine then makes the row NaN
     if (wt == 0 && g4 == 0 && lt < g.tiles_per_group && row < g.R)
-      __builtin_nontemporal_store(sum > 0.f ? (M + __log2f(sum)) * kLn2 : -INFINITY,
+      __builtin_nontemporal_store(fminf((M + __log2f(sum)) * kLn2, INFINITY),
                                   a.l_ws + part0 + row);
     if (j > 0) __syncthreads();  // the previous tiles have been read
 #pragma unroll

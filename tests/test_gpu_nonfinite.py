@@ -1,0 +1,63 @@
+"""NaN and infinite keys: every row that uses the key's page gets a NaN output and a
+NaN log-normaliser, in every launch plan and with any number of splits, and never
+the output of an empty set; every other row is as without the key, bit for bit."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# batch, KV heads, G, W, dtype, flags: one split per KV head (256 heads of 16 rows; 64
+# heads of 36 rows in the bf16 attention launch), several, the one-launch step
+SHAPES = [(32, 8, 4, 3, "bf16", 1), (32, 8, 4, 3, "f32", 1), (8, 8, 4, 8, "bf16", 1),
+          (4, 8, 8, 32, "bf16", 1), (1, 2, 4, 3, "bf16", 1), (1, 2, 4, 3, "bf16", 0),
+          (1, 2, 4, 3, "f32", 0), (1, 2, 4, 0, "bf16", 0)]
+
+
+def _run(shape, path, key):
+    """One step over 16 pages that are all kept; `key`: element 7 of one key of page 5."""
+    from paper_2508_09001_amd.layer import RetroLayer
+    b, hk, G, W, dtype, flags = shape
+    pages, P, d, t = 16, 16, 128, 200
+    lay = RetroLayer(batch=b, num_kv_heads=hk, group=G, head_dim=d, page_size=P, budget=pages * P,
+                     window=W, max_pages=pages, dtype=dtype, flags=flags)
+    g = torch.Generator().manual_seed(W + hk)
+    keys = torch.randn(b * pages, hk, P, d, generator=g)
+    if key is not None:
+        keys.view(b, pages, hk, P, d)[:, 5, :, 3, 7] = key
+    lay.k_cache.copy_(keys)
+    lay.v_cache.copy_(torch.randn(b * pages, hk, d, P, generator=g))
+    lay.seq_lens.fill_(pages * P - 1)
+    lay.last_loaded[:, :, 5] = t - W // 2 - 1        # half of the past rows may use it
+    lay.o_cache.copy_(torch.randn(lay.o_cache.shape, generator=g))
+    lay.lse_cache.copy_(torch.randn(lay.lse_cache.shape, generator=g))
+    q = torch.randn(b, W + 1, hk * G, d, generator=g)
+    q[..., 7] = q[..., 7].abs() + 0.1                # an infinite key scores +inf
+    kv = torch.randn(b, hk, d, generator=g)
+    print(f"[nonfinite] {shape} {path} {key}", flush=True)
+    if path == "step":
+        lay.step(t, q, kv, kv)
+    else:
+        lay.append(t, kv, kv)
+        lay.select(t, q[:, W])
+        lay.attend(t, q)
+        lay.merge(t)
+    torch.cuda.synchronize()
+    assert lay.num_selected.eq(pages).all()
+    uses = [r == W or t - W + r > t - W // 2 - 1 for r in range(W + 1)]
+    return uses, lay.o_out.cpu(), lay.lse_out.cpu()
+
+
+@pytest.mark.parametrize("path", ["step", "split"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_rows_that_use_a_nonfinite_key_are_nan(shape, path):
+    _, o0, z0 = _run(shape, path, None)
+    assert torch.isfinite(o0).all() and torch.isfinite(z0).all()
+    for key in (math.nan, math.inf):
+        uses, o, z = _run(shape, path, key)
+        for r, u in enumerate(uses):
+            if u:
+                assert torch.isnan(o[:, r]).all() and torch.isnan(z[:, r]).all()
+            else:
+                assert torch.equal(o[:, r], o0[:, r]) and torch.equal(z[:, r], z0[:, r])
