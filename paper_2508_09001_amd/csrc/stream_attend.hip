@@ -225,110 +225,142 @@ __global__ void __launch_bounds__(64 * NW) stream_attend_kernel(AttendArgs a, To
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) vf[dt] = *reinterpret_cast<const bf16x8*>(p + dt * 16 * P);
   };
-  if (wt < nch) {
-    load_k(wt);
-    load_v(wt);
-  }
   const bf16x8* ql = &L.q[L_t::kQ ? wr : 0][0][lane];
   // S tile t, lane row ln16: token 8 (ln16 / 4) + 4 t + ln16 % 4
   const int krow = 8 * (ln16 >> 2) + (ln16 & 3);
-  const float scale = a.scale_log2;
+  // A weight's exponent is s * scale - m in one fused operation.  m is rounded, the
+  // product in it is not: the difference can be 2^-25 |m| off either way, which
+  // from 2^31 on overflows or empties a row.  Where a maximum turned out that large
+  // the chunks are gone through once more with the scores scaled, and so
+  // rounded like m, first: 264 rows 157.6 -> 158.2 us a pass, with the question
+  // asked within the loop 160.0.
+  float pre = 1.f, scale = a.scale_log2;  // factors of a score before and in the exponent
+  int whole = 8;  // a lane with fewer stored tokens masks (and applies `pre`)
 #pragma unroll 1
-  for (int c = wt; c < nch; c += NT) {
-    const int slot = c * g.chunk_pages + vpg;
-    const int tlen = L.list.len[slot] - vslot;  // stored ones of this lane's eight tokens
-    const int mk = L.list.mask[slot];
-    f32x4 s[RT][2];
-#pragma unroll
-    for (int j = 0; j < RT; ++j)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) s[j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    stage_k();
-    const bool more = c + NT < nch;
-    if (more) load_k(c + NT);
-    // read again in every iteration: kept, they would take the registers of the
-    // accumulators
-    int qoff = 0;
-    if constexpr (L_t::kQ) asm volatile("" : "+v"(qoff));
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      bf16x8 kf[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int row = krow + 4 * t;
-        kf[t] = klds[row * KP + ((kk * 4 + g4) ^ key_swizzle(row))];
-      }
-#pragma unroll
-      for (int j = 0; j < RT; ++j) {
-        const bf16x8 qv = L_t::kQ ? ql[qoff + (j * KK + kk) * 64] : q[j][kk];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-          s[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t], qv, s[j][t], 0, 0, 0);
-      }
+  for (;;) {
+    asm volatile("" : "+s"(whole), "+s"(scale), "+s"(pre));  // one loop for both passes
+    if (wt < nch) {
+      load_k(wt);
+      load_v(wt);
     }
-    const bool part = wave_ballot(tlen < 8) != 0;
-    if (part) {  // slots past the sequence: no score, and a zero value
+#pragma unroll 1
+    for (int c = wt; c < nch; c += NT) {
+      const int slot = c * g.chunk_pages + vpg;
+      const int tlen = L.list.len[slot] - vslot;  // stored ones of this lane's eight tokens
+      const int mk = L.list.mask[slot];
+      f32x4 s[RT][2];
 #pragma unroll
       for (int j = 0; j < RT; ++j)
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t) s[j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      stage_k();
+      const bool more = c + NT < nch;
+      if (more) load_k(c + NT);
+      // read again in every iteration: kept, they would take the registers of the
+      // accumulators
+      int qoff = 0;
+      if constexpr (L_t::kQ) asm volatile("" : "+v"(qoff));
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (4 * t + i >= tlen) s[j][t][i] = -INFINITY;
+      for (int kk = 0; kk < KK; ++kk) {
+        bf16x8 kf[2];
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
+        for (int t = 0; t < 2; ++t) {
+          const int row = krow + 4 * t;
+          kf[t] = klds[row * KP + ((kk * 4 + g4) ^ key_swizzle(row))];
+        }
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (e >= tlen) vf[dt][e] = (__bf16)0.f;
-    }
-    // running maxima (the token slots of one lane lie in one page), tile by tile
-    // where a row's maximum grows; only then are the lanes' maxima combined and
-    // the accumulators rescaled.  (Rescaling later, once a maximum has grown by
-    // a margin, would be 10 % faster at 264 rows and costs accuracy: 2.4e-6
-    // against 2.0e-6 relative.)
+        for (int j = 0; j < RT; ++j) {
+          const bf16x8 qv = L_t::kQ ? ql[qoff + (j * KK + kk) * 64] : q[j][kk];
 #pragma unroll
-    for (int j = 0; j < RT; ++j) {
-      float mx = s[j][0][0];
-#pragma unroll
-      for (int i = 1; i < 8; ++i) mx = fmaxf(mx, s[j][i >> 2][i & 3]);
-      if (wave_ballot(mk < thr[j] && mx * scale > m_run[j]) != 0) {
-        const float m_new = fmaxf(m_run[j], col_max4(mk < thr[j] ? mx * scale : -INFINITY));
-        const float alpha = __builtin_amdgcn_exp2f(m_run[j] - (m_new == -INFINITY ? 0.f : m_new));
-        m_run[j] = m_new;
-        l_run[j] *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) acc[j][dt] *= alpha;
+          for (int t = 0; t < 2; ++t)
+            s[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t], qv, s[j][t], 0, 0, 0);
+        }
       }
-    }
+      if (wave_ballot(tlen < whole) != 0) {  // slots past the sequence: no score, and a zero value
 #pragma unroll
-    for (int j = 0; j < RT; ++j) {
-      const bool use = mk < thr[j];
-      const float nm = m_run[j] == -INFINITY ? 0.f : -m_run[j];
-      uint32_t ph[4], pl[4];  // the weights' bf16 upper parts and remainders, in pairs
-      float psum = 0.f;
+        for (int j = 0; j < RT; ++j)
 #pragma unroll
-      for (int e = 0; e < 8; e += 2) {
-        // the hardware exp2 (v_exp_f32): a weight under 2^-126 becomes 0
-        const float x0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j][e >> 2][e & 3], scale, nm));
-        const float x1 =
-            __builtin_amdgcn_exp2f(__builtin_fmaf(s[j][e >> 2][(e & 3) + 1], scale, nm));
-        const float p0 = use ? x0 : 0.f, p1 = use ? x1 : 0.f;
-        psum += p0 + p1;
-        ph[e / 2] = pack_bf16(p0, p1);
-        pl[e / 2] = pack_bf16(p0 - __uint_as_float(ph[e / 2] << 16),
-                              p1 - __uint_as_float(ph[e / 2] & 0xFFFF0000u));
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (4 * t + i >= tlen) s[j][t][i] = -INFINITY;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (e >= tlen) vf[dt][e] = (__bf16)0.f;
+#pragma unroll
+        for (int j = 0; j < RT; ++j)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) s[j][t] *= pre;
       }
-      const bf16x8 phv = __builtin_bit_cast(bf16x8, u32x4v{ph[0], ph[1], ph[2], ph[3]});
-      const bf16x8 plv = __builtin_bit_cast(bf16x8, u32x4v{pl[0], pl[1], pl[2], pl[3]});
-      l_run[j] += psum;
+      // running maxima (the token slots of one lane lie in one page), tile by tile
+      // where a row's maximum grows; only then are the lanes' maxima combined and
+      // the accumulators rescaled.  (Rescaling later, once a maximum has grown by
+      // a margin, would be 10 % faster at 264 rows and costs accuracy: 2.4e-6
+      // against 2.0e-6 relative.)
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        acc[j][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], phv, acc[j][dt], 0, 0, 0);
+      for (int j = 0; j < RT; ++j) {
+        float mx = s[j][0][0];
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        acc[j][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], plv, acc[j][dt], 0, 0, 0);
+        for (int i = 1; i < 8; ++i) mx = fmaxf(mx, s[j][i >> 2][i & 3]);
+        if (wave_ballot(mk < thr[j] && mx * scale > m_run[j]) != 0) {
+          const float m_new = fmaxf(m_run[j], col_max4(mk < thr[j] ? mx * scale : -INFINITY));
+          const float alpha = __builtin_amdgcn_exp2f(m_run[j] - (m_new == -INFINITY ? 0.f : m_new));
+          m_run[j] = m_new;
+          l_run[j] *= alpha;
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) acc[j][dt] *= alpha;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < RT; ++j) {
+        const bool use = mk < thr[j];
+        const float nm = m_run[j] == -INFINITY ? 0.f : -m_run[j];
+        uint32_t ph[4], pl[4];  // the weights' bf16 upper parts and remainders, in pairs
+        float psum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          // the hardware exp2 (v_exp_f32): a weight under 2^-126 becomes 0
+          const float x0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j][e >> 2][e & 3], scale, nm));
+          const float x1 =
+              __builtin_amdgcn_exp2f(__builtin_fmaf(s[j][e >> 2][(e & 3) + 1], scale, nm));
+          const float p0 = use ? x0 : 0.f, p1 = use ? x1 : 0.f;
+          psum += p0 + p1;
+          ph[e / 2] = pack_bf16(p0, p1);
+          pl[e / 2] = pack_bf16(p0 - __uint_as_float(ph[e / 2] << 16),
+                                p1 - __uint_as_float(ph[e / 2] & 0xFFFF0000u));
+        }
+        const bf16x8 phv = __builtin_bit_cast(bf16x8, u32x4v{ph[0], ph[1], ph[2], ph[3]});
+        const bf16x8 plv = __builtin_bit_cast(bf16x8, u32x4v{pl[0], pl[1], pl[2], pl[3]});
+        l_run[j] += psum;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+          acc[j][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], phv, acc[j][dt], 0, 0, 0);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+          acc[j][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], plv, acc[j][dt], 0, 0, 0);
+      }
+      if (more) load_v(c + NT);
     }
-    if (more) load_v(c + NT);
+    bool large = false;
+#pragma unroll
+    for (int j = 0; j < RT; ++j)
+      large = large || (fabsf(m_run[j]) > 0x1p20f && fabsf(m_run[j]) < INFINITY);
+    if (whole == 8 && wave_ballot(large) != 0) {
+      whole = 0x7fffffff;
+      pre = scale;
+      scale = 1.f;
+#pragma unroll
+      for (int j = 0; j < RT; ++j) {
+        m_run[j] = -INFINITY;
+        l_run[j] = 0.f;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) acc[j][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    } else {
+      break;
+    }
   }
 
   // ---- merge the wavefronts' states: factors per row, then the outputs tile by

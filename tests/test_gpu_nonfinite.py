@@ -1,6 +1,7 @@
 """NaN and infinite keys: every row that uses the key's page gets a NaN output and a
 NaN log-normaliser, in every launch plan and with any number of splits, and never
-the output of an empty set; every other row is as without the key, bit for bit."""
+the output of an empty set; every other row is as without the key, bit for bit.
+Scores of any finite size give finite outputs."""
 import math
 
 import pytest
@@ -61,3 +62,43 @@ def test_rows_that_use_a_nonfinite_key_are_nan(shape, path):
                 assert torch.isnan(o[:, r]).all() and torch.isnan(z[:, r]).all()
             else:
                 assert torch.equal(o[:, r], o0[:, r]) and torch.equal(z[:, r], z0[:, r])
+
+
+# Scores far beyond the range in which a difference of two of them is exact in fp32:
+# the largest one's key takes the whole weight, and the log-normaliser is its score.
+@pytest.mark.parametrize("power", [4, 13, 18, 30])
+@pytest.mark.parametrize("shape", [(8, 8, 4, 8, "bf16", 1), (4, 8, 8, 32, "bf16", 1),
+                                   (32, 8, 4, 3, "f32", 1), (1, 2, 4, 3, "bf16", 0)])
+def test_large_scores(shape, power):
+    from paper_2508_09001_amd.layer import RetroLayer
+    b, hk, G, W, dtype, flags = shape
+    pages, P, d, t = 16, 16, 128, 200
+    lay = RetroLayer(batch=b, num_kv_heads=hk, group=G, head_dim=d, page_size=P, budget=pages * P,
+                     window=W, max_pages=pages, dtype=dtype, flags=flags)
+    g = torch.Generator().manual_seed(W + hk + power)
+    lay.k_cache.copy_(torch.randn(b * pages, hk, P, d, generator=g) * 2.0 ** power)
+    lay.v_cache.copy_(torch.randn(b * pages, hk, d, P, generator=g))
+    lay.seq_lens.fill_(pages * P - 1)
+    q = (torch.randn(b, W + 1, hk * G, d, generator=g) * 2.0 ** power).to(lay.dtype)
+    kv = torch.randn(b, hk, d, generator=g)
+    print(f"[large] {shape} 2^{power}", flush=True)
+    lay.step(t, q, kv, kv)
+    torch.cuda.synchronize()
+    K = lay.k_cache.cpu().double().view(b, pages, hk, P, d).transpose(1, 2).reshape(b, hk, -1, d)
+    V = lay.v_cache.cpu().double().view(b, pages, hk, d, P).permute(0, 2, 1, 4, 3)
+    V = V.reshape(b, hk, -1, d)
+    Q = q.double().view(b, W + 1, hk, G, d).permute(0, 2, 1, 3, 4).reshape(b, hk, -1, d)
+    x = Q @ K.transpose(2, 3) / math.sqrt(d)
+    x[:, :, :W * G, -P:] = -math.inf     # past queries do not use the page of the step's token
+    # a score's error: d products and sums in fp32, the scaling and the rounding
+    err = 2.0 ** -24 * (d + 4) * (Q.abs() @ K.abs().transpose(2, 3)).amax(-1) / math.sqrt(d)
+    top = x.topk(2, dim=-1)
+    clear = top.values[..., 0] - top.values[..., 1] > 2 * err + 40    # the others weigh nothing
+    want = V.gather(2, top.indices[..., :1].expand(-1, -1, -1, d))
+    o = lay.o_out.cpu().double().view(b, W + 1, hk, G, d).permute(0, 2, 1, 3, 4).reshape(want.shape)
+    z = lay.lse_out.cpu().double().view(b, W + 1, hk, G).permute(0, 2, 1, 3).reshape(*clear.shape)
+    assert torch.isfinite(o).all() and torch.isfinite(z).all()
+    assert clear.double().mean() > (0.9 if power > 4 else 0.5)
+    # one weight of 1 within the rounding of its bf16 parts
+    assert ((o - want).abs() <= 2.0 ** -15 * want.abs() + 1e-6)[clear].all()
+    assert ((z - x.amax(-1)).abs() <= err + math.log(pages * P) + 2.0 ** -22 * z.abs()).all()
