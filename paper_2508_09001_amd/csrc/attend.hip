@@ -205,7 +205,9 @@ hipError_t launch_attend_select(const Geometry& g, int step, const void* q_windo
   a.sel_phys = tok_out;  // non-null: the page list carries physical pages (never read here)
   const TopkArgs ta{g, step, scores, c.page_table, c.last_loaded, sel.selected, sel.mask,
                     sel.num_selected, nullptr, 0, tok_out};
-  if (g.dtype == RETRO_BF16) return launch_stream_attend(a, &ta, s);
+  if (g.stream) return launch_stream_attend(a, &ta, s);
+  if (g.dtype == RETRO_BF16)
+    return g.D == 128 ? attend_select_d<bf16_t, 128>(a, ta, s) : attend_select_d<bf16_t, 64>(a, ta, s);
   return g.D == 128 ? attend_select_d<float, 128>(a, ta, s) : attend_select_d<float, 64>(a, ta, s);
 }
 

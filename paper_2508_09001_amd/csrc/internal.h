@@ -114,8 +114,8 @@ hipError_t launch_attend(const Geometry& g, int step, const void* q_window,
                          hipStream_t s);
 // The attention of the multi-launch plans for bf16 layers (stream_attend.hip) has
 // a split of its own: attend_geometry(g) is g with that split (g itself for
-// fp32 and where attend_kernel is the faster one), to be used for launch_attend and the combine of its partials.
-// `selects`: for launch_attend_select.
+// fp32 and where attend_kernel is the faster one), to be used for the attention
+// launch and the combine of its partials.  `selects`: for launch_attend_select.
 Geometry attend_geometry(const Geometry& g, bool selects = false);
 // Attention with the page selection (top-k + Alg. 2's mask) made by each of its
 // workgroups from the score launch's page scores (attend_selects(g); g from

@@ -450,21 +450,39 @@ hipError_t go_d(const AttendArgs& a, const TopkArgs* ta, hipStream_t s) {
 }  // namespace
 
 namespace {
-// Without a selection in front, splits of a few chunks go to attend_kernel: a
-// wavefront's merge of several row tiles here is long straight-line code that
-// runs once.  g: attend_kernel's split, x: the row tiles here.  Attention and
-// combine, 8 KV heads, attend_kernel / here in us: 36 rows, 8 pages 8.4 / 12.8, 128
-// pages (two chunks a split) 12.6 / 15.8, 256 pages (four) 15.5 / 17.0, 512 pages
-// (eight) 22.4 / 20.4; 68 rows, 128 pages 14.8 / 16.7, 512 pages 26.6 / 23.0.  136
-// rows (two tiles a wavefront there), 32 pages 14.0 / 15.7 with half the compute
-// units, 64 pages 17.7 / 16.3 with all; 100 rows (two tiles a wavefront here), 8
-// pages 9.8 / 11.4 with an eighth, 32 pages 12.9 / 12.5 with half.  One tile a
-// wavefront here: 7.8 / 7.5 to 20.5 / 13.8, never there.
-bool attend_kernel_wins(const Geometry& g, const Geometry& x) {
+// Splits of a few chunks go to attend_kernel (attend_select_kernel): a wavefront's
+// merge of several row tiles here is long straight-line code that runs once.  g:
+// attend_kernel's split, x: the row tiles here.  One tile a wavefront here is never
+// the slower one.
+//
+// Without a selection in front, attention and combine, 8 KV heads, attend_kernel /
+// here in us: 36 rows, 8 pages 8.4 / 12.8, 128 pages (two chunks a split) 12.6 /
+// 15.8, 256 pages (four) 15.5 / 17.0, 512 pages (eight) 22.4 / 20.4; 68 rows, 128
+// pages 14.8 / 16.7, 512 pages 26.6 / 23.0.  136 rows (two tiles a wavefront
+// there), 32 pages 14.0 / 15.7 with half the compute units, 64 pages 17.7 / 16.3
+// with all; 100 rows (two tiles a wavefront here), 8 pages 9.8 / 11.4 with an
+// eighth, 32 pages 12.9 / 12.5 with half.
+//
+// With one, the whole step of three launches at 300 pages, KV heads x rows x pages
+// kept: three tiles a wavefront here, 8 x 36 x 64 19.7 / 21.9, 32 x 36 x 64 (four
+// chunks a split) 24.4 / 25.2, 64 x 36 x 64 (eight) 30.8 / 28.6, 2 x 36 x 128 (64
+// splits) 20.5 / 21.9, 2 x 36 x 256 (128 splits) 23.3 / 22.7; two tiles a wavefront
+// here, 8 x 32 x 64 19.6 / 20.1, 32 x 32 x 32 (two chunks a split) 21.4 / 22.0, 32 x
+// 32 x 64 (four) 23.9 / 23.1, 2 x 32 x 128 (64 splits) 20.4 / 20.0; two tiles a
+// wavefront there, 8 x 136 x 32 21.1 / 22.5 with half the compute units, 64 pages
+// 23.9 / 23.0 with all, 16 x 260 x 16 (two row groups) 23.7 / 24.7 with all, 2 x 260
+// x 128 (64 splits) 24.0 / 23.2.
+bool attend_kernel_wins(const Geometry& g, const Geometry& x, bool selects) {
   const int cap = compute_units();
   const int64_t wgs = (int64_t)g.batch * g.hk * g.n_rgroups * g.n_splits;
   if (wgs > cap || x.tiles_per_group == 1) return false;
   const bool three = x.tiles_per_group == 3 || x.tiles_per_group > 4;  // tiles a wavefront (go_d)
+  if (selects) {
+    if (g.rtw > 1)
+      return g.chunks_per_split == 1 && g.n_splits <= 32 && 2 * wgs <= (int64_t)cap * g.n_rgroups;
+    return three ? g.chunks_per_split <= 4 && g.n_splits <= 64
+                 : g.chunks_per_split <= 2 && g.n_splits <= 32;
+  }
   if (three && g.rtw == 1) return g.chunks_per_split <= 4;
   return g.chunks_per_split == 1 && wgs <= (three ? cap / 2 : cap / 4);
 }
@@ -477,7 +495,7 @@ Geometry attend_geometry(const Geometry& g, bool selects) {
   x.n_rgroups = (g.row_tiles + kMaxTiles - 1) / kMaxTiles;
   x.tiles_per_group = (g.row_tiles + x.n_rgroups - 1) / x.n_rgroups;
   const int nw = x.tiles_per_group <= 3 ? NW : NW / 2;  // wavefronts over the chunks (go_d)
-  if (!selects && attend_kernel_wins(g, x)) return g;
+  if (attend_kernel_wins(g, x, selects)) return g;
   x.stream = 1;
   // One workgroup per compute unit (its registers); the split count with the
   // smallest time, counted in chunk iterations of a wavefront: rounds of
