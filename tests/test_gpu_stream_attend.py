@@ -130,9 +130,9 @@ def test_nan_key_reaches_the_rows_that_use_it(W, G):
             assert ((o[r, h * G:(h + 1) * G] - w @ V).abs() <= bound).all()
 
 
-# table lengths around the stripes of the selection (512 pages each: 2, 5, 9, 12)
+# table lengths around the stripes of the selection (512 pages each: 2, 5, 6, 9, 12)
 # and past the last one (a launch of its own)
-@pytest.mark.parametrize("mp", [33, 512, 513, 1024, 1025, 2561, 4608, 4700, 6144, 6145])
+@pytest.mark.parametrize("mp", [33, 512, 513, 1024, 1025, 2561, 3072, 3073, 4608, 4700, 6144, 6145])
 @pytest.mark.parametrize("path", ["select", "step"])
 def test_selection_matches_sorted_scores(mp, path):
     P, B, t = 16, 48 * 16, 9
