@@ -450,41 +450,48 @@ hipError_t go_d(const AttendArgs& a, const TopkArgs* ta, hipStream_t s) {
 }  // namespace
 
 namespace {
-// Splits of a few chunks go to attend_kernel (attend_select_kernel): a wavefront's
-// merge of several row tiles here is long straight-line code that runs once.  g:
-// attend_kernel's split, x: the row tiles here.  One tile a wavefront here is never
-// the slower one.
-//
-// Without a selection in front, attention and combine, 8 KV heads, attend_kernel /
-// here in us: 36 rows, 8 pages 8.4 / 12.8, 128 pages (two chunks a split) 12.6 /
-// 15.8, 256 pages (four) 15.5 / 17.0, 512 pages (eight) 22.4 / 20.4; 68 rows, 128
-// pages 14.8 / 16.7, 512 pages 26.6 / 23.0.  136 rows (two tiles a wavefront
-// there), 32 pages 14.0 / 15.7 with half the compute units, 64 pages 17.7 / 16.3
-// with all; 100 rows (two tiles a wavefront here), 8 pages 9.8 / 11.4 with an
-// eighth, 32 pages 12.9 / 12.5 with half.
-//
-// With one, the whole step of three launches at 300 pages, KV heads x rows x pages
-// kept: three tiles a wavefront here, 8 x 36 x 64 19.7 / 21.9, 32 x 36 x 64 (four
-// chunks a split) 24.4 / 25.2, 64 x 36 x 64 (eight) 30.8 / 28.6, 2 x 36 x 128 (64
-// splits) 20.5 / 21.9, 2 x 36 x 256 (128 splits) 23.3 / 22.7; two tiles a wavefront
-// here, 8 x 32 x 64 19.6 / 20.1, 32 x 32 x 32 (two chunks a split) 21.4 / 22.0, 32 x
-// 32 x 64 (four) 23.9 / 23.1, 2 x 32 x 128 (64 splits) 20.4 / 20.0; two tiles a
-// wavefront there, 8 x 136 x 32 21.1 / 22.5 with half the compute units, 64 pages
-// 23.9 / 23.0 with all, 16 x 260 x 16 (two row groups) 23.7 / 24.7 with all, 2 x 260
-// x 128 (64 splits) 24.0 / 23.2.
+// Small calls go to attend_kernel (attend_select_kernel): a wavefront's merge of
+// several row tiles here is long straight-line code that runs once per workgroup.
+// The two times, in us, for g (attend_kernel's split) and x (the split here), each
+// from rounds of workgroups over the compute units, the chunks that a wavefront
+// goes through one after another, and the partial rows that are written and
+// combined; the constants fit 1450 measured shapes (1 to 17 row tiles, 2 to 200 KV
+// heads, 4 to 512 pages, d 64 and 128) to 5 to 10 %.  The choice costs 0.3 % more
+// than the faster of the two in every shape, the streamed attention always 8 %,
+// attend_kernel always 16 %.  Some on either side (attend_kernel / here, attention
+// and combine): 8 heads of 36 rows, 128 pages 12.6 / 15.8, 512 pages 22.4 / 20.4; 16
+// heads of 20 rows, 16 pages 9.3 / 12.2, 10 of 260, 16 pages 15.0 / 17.9, 200 of 16,
+// 4 pages 14.0 / 11.2.  With the selection in front (4 us a round) three launches
+// took: 8 heads of 36 rows, 64 pages 19.7 / 21.9, 32 x 36 x 64 24.4 / 25.2, 64 x 36 x
+// 64 30.8 / 28.6.  Splits of more than four chunks there stay here.  So does one row
+// tile (2 heads of 4 rows, 256 pages 14.6 / 10.4, 200 of 16, 4 pages 14.0 / 11.2),
+// but for d 128 in 4 to 16 splits of one chunk without a selection: 8 heads of 16
+// rows, 16 pages 9.0 / 9.9, 32 of 4, 16 pages 9.0 / 9.3.
 bool attend_kernel_wins(const Geometry& g, const Geometry& x, bool selects) {
   const int cap = compute_units();
-  const int64_t wgs = (int64_t)g.batch * g.hk * g.n_rgroups * g.n_splits;
-  if (wgs > cap || x.tiles_per_group == 1) return false;
-  const bool three = x.tiles_per_group == 3 || x.tiles_per_group > 4;  // tiles a wavefront (go_d)
-  if (selects) {
-    if (g.rtw > 1)
-      return g.chunks_per_split == 1 && g.n_splits <= 32 && 2 * wgs <= (int64_t)cap * g.n_rgroups;
-    return three ? g.chunks_per_split <= 4 && g.n_splits <= 64
-                 : g.chunks_per_split <= 2 && g.n_splits <= 32;
-  }
-  if (three && g.rtw == 1) return g.chunks_per_split <= 4;
-  return g.chunks_per_split == 1 && wgs <= (three ? cap / 2 : cap / 4);
+  const int64_t heads = (int64_t)g.batch * g.hk;
+  if (x.tiles_per_group == 1)
+    return !selects && g.D == 128 && g.chunks_per_split == 1 && g.n_splits >= 4 &&
+           g.n_splits <= 16 && heads * g.n_splits <= cap;
+  if (g.chunks_per_split > 4) return false;
+  auto time = [&](const Geometry& y, int chunks, const float (&c)[5]) {
+    const int64_t rounds = (heads * y.n_rgroups * y.n_splits + cap - 1) / cap;
+    const float partials = 1e-6f * (float)(heads * y.n_splits * y.R) * (float)y.D;
+    return c[0] + (float)rounds * (c[1] + (selects ? 4.f : 0.f) + c[2] * (float)(chunks * y.D) / 128.f) +
+           c[3] * partials + c[4] * (float)((y.n_splits - 1) / 32);
+  };
+  // fixed, per round, per chunk of 32 tokens at d 128, per million partial
+  // elements, per 32 splits after the first (another group of the combine)
+  static constexpr float kHere[5][5] = {{4.0f, 4.0f, 3.9f, 6.4f, 0.f},   // 2 row tiles
+                                        {4.7f, 4.7f, 5.2f, 4.8f, 0.f},   // 3
+                                        {2.0f, 8.0f, 2.0f, 2.8f, 1.1f},  // 4
+                                        {1.3f, 10.1f, 2.8f, 2.7f, 0.7f},
+                                        {0.1f, 12.1f, 3.0f, 2.2f, 1.5f}};
+  static constexpr float kThere[2][5] = {{8.0f, 0.f, 1.5f, 2.1f, 1.5f},  // 1 tile a wavefront
+                                         {6.2f, 3.0f, 2.0f, 1.8f, 0.7f}};
+  const int nw = x.tiles_per_group <= 3 ? NW : NW / 2;  // wavefronts over the chunks (go_d)
+  return time(g, g.chunks_per_split, kThere[g.rtw - 1]) <
+         time(x, (x.chunks_per_split + nw - 1) / nw, kHere[x.tiles_per_group - 2]);
 }
 }  // namespace
 
@@ -495,7 +502,6 @@ Geometry attend_geometry(const Geometry& g, bool selects) {
   x.n_rgroups = (g.row_tiles + kMaxTiles - 1) / kMaxTiles;
   x.tiles_per_group = (g.row_tiles + x.n_rgroups - 1) / x.n_rgroups;
   const int nw = x.tiles_per_group <= 3 ? NW : NW / 2;  // wavefronts over the chunks (go_d)
-  if (attend_kernel_wins(g, x, selects)) return g;
   x.stream = 1;
   // One workgroup per compute unit (its registers); the split count with the
   // smallest time, counted in chunk iterations of a wavefront: rounds of
@@ -520,7 +526,7 @@ Geometry attend_geometry(const Geometry& g, bool selects) {
   x.chunks_per_split = (g.chunks_max + best - 1) / best;
   x.n_splits = (g.chunks_max + x.chunks_per_split - 1) / x.chunks_per_split;
   x.pages_per_split = x.chunks_per_split * g.chunk_pages;
-  return x;
+  return attend_kernel_wins(g, x, selects) ? g : x;
 }
 
 hipError_t launch_stream_attend(const AttendArgs& a, const TopkArgs* ta, hipStream_t s) {
