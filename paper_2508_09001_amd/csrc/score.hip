@@ -28,12 +28,16 @@ constexpr int kPassPages = kScoreWaves * 4;              // pages of a pass
 constexpr int kMaxPpb = kPassPages * kScoreIters;        // most pages a workgroup scores
 
 // Workgroups per KV head and pages per workgroup: two workgroups for every
-// compute unit while a pass each is left, at most kMaxPpb pages a workgroup.
-void score_split(const Geometry& g, int* nbh, int* ppb) {
-  const int heads = g.hk * g.batch;
+// compute unit while a pass each is left, at most kMaxPpb pages a workgroup.  With
+// the selection at the end, one for every compute unit where that is enough, of
+// whole passes: 32 heads of 300 pages 8.7 us, 9.6 with two; 2 heads of 5900 pages
+// 13.8, in workgroups of 47 pages 14.2, of 24 15.7.
+void score_split(const Geometry& g, bool selects, int* nbh, int* ppb) {
+  const int heads = g.hk * g.batch, cus = compute_units();
   const int n_min = (g.max_pages + kMaxPpb - 1) / kMaxPpb;
   const int n_max = (g.max_pages + kPassPages - 1) / kPassPages;
-  const int n = std::min(n_max, std::max(n_min, 2 * compute_units() / heads));
+  int n = std::min(n_max, std::max(n_min, 2 * cus / heads));
+  if (selects && (int64_t)n_max * heads > cus && (int64_t)n_min * heads <= cus) n = n_min;
   *ppb = (g.max_pages + n - 1) / n;
   *nbh = (g.max_pages + *ppb - 1) / *ppb;
 }
@@ -119,7 +123,7 @@ hipError_t score_t(const Geometry& g, const void* q, int64_t qbs, const retro_kv
                    const void* k_new, const void* v_new, float* scores, const SelectArgs& sa,
                    hipStream_t s) {
   int nbh, ppb;
-  score_split(g, &nbh, &ppb);
+  score_split(g, PER > 0, &nbh, &ppb);
   if (ppb < 1 || ppb > kMaxPpb || nbh < 1) return hipErrorInvalidValue;
   dim3 grid(nbh, g.hk, g.batch);
   size_t lds = sizeof(float) * 2 * g.G * D;  // the queries' q+ and q- halves
@@ -138,6 +142,8 @@ hipError_t score_d(const Geometry& g, const void* q, int64_t qbs, const retro_kv
     return score_t<T, D, decltype(per)::value>(g, q, qbs, c, k_new, v_new, scores, sa, s);
   };
   if (!sa.count) return go(std::integral_constant<int, 0>{});
+  // (300 pages with two a thread: 8.4 us instead of 8.0)
+  if (g.max_pages <= kScoreThreads) return go(std::integral_constant<int, 1>{});
   return with_select_per(g.max_pages, go);
 }
 
@@ -157,11 +163,14 @@ int compute_units() {
 }
 
 // Up to here a call's host time, a launch fewer, is what the last workgroup's
-// selection saves; from about twice as many pages the chain from a head's last
-// score to its rows costs more (16K pages of 16 heads 10.3 against 11.6 us, 33K
-// pages 16.0 against 13.8, 131K pages 41 against 28).
+// selection saves at equal time on the GPU (128 heads of 250 pages 11.4 us both, 32
+// of 600 11.2 against 10.9 with a launch of its own, 2 of 4100 12.2 against 12.4);
+// past it the chain from a head's last score to its rows costs more (16 heads of
+// 2000 pages 13.7 against 13.1, 8 of 4090 16.7 against 15.0, 33K pages 16.0 against
+// 13.8, 131K 41 against 28).
 bool score_selects(const Geometry& g) {
-  return (int64_t)g.batch * g.hk * g.max_pages <= 1 << 15 && g.max_pages <= kScoreThreads * kSelectPer;
+  const int64_t pages = (int64_t)g.batch * g.hk * g.max_pages;
+  return pages <= (g.max_pages <= 1024 ? 1 << 15 : 1 << 14) && g.max_pages <= kScoreThreads * kSelectPer;
 }
 
 hipError_t launch_score(const Geometry& g, const void* q_cur, int64_t q_batch_stride,
