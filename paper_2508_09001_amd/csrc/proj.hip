@@ -125,10 +125,11 @@ __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
   // loads are short either way and the pass through LDS would be the longer one
   constexpr bool OPER = MT == 1 && !OUT;
   constexpr int UA = OPER || rows_unroll(MT, OUT, CT) > U ? U : rows_unroll(MT, OUT, CT);
-  constexpr int TPR = NW * 64 / 256;  // output tiles summed per round, 256 threads each
+  // output tiles summed per round, 256 threads each
+  constexpr int TPR = NW * 64 / 256 < CT * MT ? NW * 64 / 256 : CT * MT;
   // each wavefront's row tiles in turn; the shares of TPR tiles afterwards
   __shared__ __attribute__((aligned(16))) union {
-    u32x4 x[NW][MT][64];
+    u32x4 x[OPER ? 1 : NW][OPER ? 1 : MT][64];
     float red[TPR][NW * SH][4][64];
   } L;
   __shared__ int s_len[UPD ? PJ_MAX_BATCH : 1];
@@ -196,7 +197,7 @@ __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
   // tile mt is row mt*16 + 4*(l/16) + i, column (tile0 + c)*16 + l%16
 #pragma unroll
   for (int p0 = 0; p0 < CT * MT; p0 += TPR) {
-    __syncthreads();  // the row tiles (or the previous round's sums) are read
+    if (!OPER || p0 > 0) __syncthreads();  // the row tiles (or the previous round's sums) are read
 #pragma unroll
     for (int t = 0; t < TPR; ++t)
       if (p0 + t < CT * MT)
@@ -208,7 +209,7 @@ __global__ void __launch_bounds__(64 * NW) proj_kernel(ProjArgs a) {
     __syncthreads();
     const int pass = p0 + (int)(threadIdx.x >> 8), c = pass / MT, mt = pass % MT;
     const int o = threadIdx.x & 255;
-    if (pass >= CT * MT) continue;
+    if (pass >= CT * MT || pass - p0 >= TPR) continue;
     const int i = o >> 6, l = o & 63;
     const int row = mt * 16 + 4 * (l >> 4) + i;
     if (row >= a.rows) continue;
@@ -634,8 +635,12 @@ retro_status retro_project_f32(const float* x, int32_t rows, int32_t k, const fl
       project_f32_kernel<RB, false><<<grid, kF32Loaders + RB * kF32Cols, 0, (hipStream_t)stream>>>(
           x, rows, k, w, n, y, accumulate ? 1 : 0);
   };
-  // few rows: a quarter of the LDS and of the row loads
-  if (rows <= 8) go(std::integral_constant<int, 8>{});
+  // Blocks of eight rows, a quarter of the LDS reads per workgroup, where a compute
+  // unit is left for each: 33 rows, 64 x 64 5.2 -> 4.4 us, 17 rows, 4096 x 1024 45 ->
+  // 21; with more workgroups the weight's second reading costs more (70 rows, 4096 x
+  // 1024 46 -> 54).
+  const int64_t eights = (int64_t)((n + kF32Cols - 1) / kF32Cols) * ((rows + 7) / 8);
+  if (rows <= 8 || eights <= retro::compute_units()) go(std::integral_constant<int, 8>{});
   else go(std::integral_constant<int, 32>{});
   return retro::status_of(hipGetLastError());
 }

@@ -59,7 +59,10 @@ def test_prefill_chunks(dtype, P, d, off):
 # 256 and the four of a trip; off 1: w not 16-byte aligned
 @pytest.mark.parametrize("rows,K,n,off", [(1, 1, 1, 0), (5, 255, 16, 0), (8, 256, 20, 0),
                                           (9, 257, 31, 0), (32, 1024, 48, 1), (33, 1027, 32, 0),
-                                          (70, 2049, 17, 1), (3, 1280, 64, 1)])
+                                          (70, 2049, 17, 1), (3, 1280, 64, 1),
+                                          # more blocks of eight rows than compute units
+                                          (9, 257, 2201, 0), (33, 300, 1000, 0),
+                                          (70, 1027, 500, 1)])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_project_f32_is_the_documented_chain(rows, K, n, off, accumulate):
     from paper_2508_09001_amd import binding as B
