@@ -390,9 +390,10 @@ __global__ void __launch_bounds__(64 * NW) stream_attend_kernel(AttendArgs a, To
       sum += L.l[w * NR + wr][rr] * __builtin_amdgcn_exp2f(L.m[w * NR + wr][rr] - Mu);
     const float f = sum > 0.f ? __builtin_amdgcn_exp2f(m_run[j] - Mu) / sum : 0.f;
     // -inf for an empty sum; +inf (fminf skips NaN) for a NaN one, from NaN or
-    // infinite scores: the combine then makes the row NaN
+    // infinite scores: the combine then makes the row NaN.  One rounding at the
+    // normaliser's size, since with few splits none average out.
     if (wt == 0 && g4 == 0 && lt < g.tiles_per_group && row < g.R)
-      __builtin_nontemporal_store(fminf((M + __log2f(sum)) * kLn2, INFINITY),
+      __builtin_nontemporal_store(fminf(__builtin_fmaf(M, kLn2, __log2f(sum) * kLn2), INFINITY),
                                   a.l_ws + part0 + row);
     if (j > 0) __syncthreads();  // the previous tiles have been read
 #pragma unroll
