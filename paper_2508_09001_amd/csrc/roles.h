@@ -149,19 +149,6 @@ __device__ __forceinline__ int wave_inclusive_scan(int x) {
   return x;
 }
 
-// Exclusive prefix sum over the workgroup (at most 16 wavefronts); sh >= 16 ints.
-__device__ __forceinline__ int block_exclusive_scan(int v, int* sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const int x = wave_inclusive_scan(v);
-  if (lane == 63) sh[wave] = x;
-  __syncthreads();
-  int off = 0;
-  for (int w = 0; w < nw; ++w)
-    if (w < wave) off += sh[w];
-  __syncthreads();
-  return off + x - v;
-}
-
 // ============================================================================
 // Score role: eq. (quest_score) for a block of consecutive logical pages of one
 // (sequence, KV head), in the fixed fp32 order (products rounded, pairwise sum

@@ -77,7 +77,7 @@ __global__ void __launch_bounds__(kScoreThreads, PER ? 4 : 8) score_kernel(
     const int pos = seq_lens[b];
     StepToken<T> tk{-1, 0, nullptr, nullptr, nullptr, nullptr};
     int seq_len = pos;
-    if (g.token_pending) {
+    if (PER == 0 && g.token_pending) {  // (no step selects in its score launch)
       const int phys = token_phys(g, ta.pt, b, pos);
       if (phys >= 0) {
         seq_len = pos + 1;
@@ -179,7 +179,7 @@ hipError_t launch_score(const Geometry& g, const void* q_cur, int64_t q_batch_st
                         int32_t* counters) {
   SelectArgs sa{};
   if (sel) {
-    if (!counters || !score_selects(g)) return hipErrorInvalidValue;
+    if (!counters || !score_selects(g) || g.token_pending) return hipErrorInvalidValue;
     sa.tk = TopkArgs{g, step, scores, c.page_table, c.last_loaded, sel->selected, sel->mask,
                      sel->num_selected, nullptr, 1, nullptr};
     sa.count = counters;
