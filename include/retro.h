@@ -346,6 +346,16 @@ retro_status retro_step(const retro_dims* dims, int32_t step, const void* q_wind
  * *launches.  Host only: nothing is enqueued. */
 retro_status retro_step_launches(const retro_dims* dims, int32_t* launches);
 
+/* How the attention of these dims is launched on the current device: *row_tiles
+ * = the tiles of 16 window rows that a workgroup of the streamed kernel takes, or
+ * 0 where the kernel that stages chunks through LDS takes the call (fp32, and
+ * small calls for which it is the faster one); *splits = the parts of the
+ * selection per KV head.  selects == 0: retro_decode_attend and the attention
+ * launch of steps without a selection in front of it; else the attention of a
+ * step of three launches.  Host only: nothing is enqueued. */
+retro_status retro_attend_plan(const retro_dims* dims, int32_t selects, int32_t* row_tiles,
+                               int32_t* splits);
+
 /* retro_step for callers that cannot allocate (code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation): the same step and
  * results, with the workspace in a static device array of the library (64 MiB

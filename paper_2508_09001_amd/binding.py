@@ -10,7 +10,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
-from typing import Optional
+from typing import Optional, Tuple
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libretro_mi355x.so")
@@ -25,8 +25,8 @@ EXPORTED = ("retro_version", "retro_status_string", "retro_k_max", "retro_worksp
             "retro_select_pages",
             "retro_decode_attend", "retro_decode_attend_partials", "retro_step_attend_partials",
             "retro_copy_scores", "retro_merge_output_cache", "retro_step", "retro_step_noalloc",
-            "retro_step_launches", "retro_pack_weight", "retro_project_qkv",
-            "retro_project_qkv_update", "retro_project_out", "retro_project_f32")
+            "retro_step_launches", "retro_attend_plan", "retro_pack_weight",
+            "retro_project_qkv", "retro_project_qkv_update", "retro_project_out", "retro_project_f32")
 
 
 class RetroError(RuntimeError):
@@ -99,6 +99,7 @@ def load_library(path: str = LIB_PATH):
         "retro_step_noalloc": ([D, i32, P, P, P, C.POINTER(KVCache), C.POINTER(Selection),
                                 C.POINTER(OutputCache), P, P, P], C.c_int),
         "retro_step_launches": ([D, C.POINTER(C.c_int32)], C.c_int),
+        "retro_attend_plan": ([D, i32, C.POINTER(C.c_int32), C.POINTER(C.c_int32)], C.c_int),
         "retro_pack_weight": ([P, i32, i32, P, P], C.c_int),
         "retro_project_qkv": ([P, i32, i32, P, i32, i32, P, P, P, P], C.c_int),
         "retro_project_out": ([P, i32, i32, P, i32, P, P, P], C.c_int),
@@ -238,6 +239,15 @@ def retro_step_launches(dims: Dims) -> int:
     n = C.c_int32(0)
     _check(load_library().retro_step_launches(C.byref(dims), C.byref(n)), "retro_step_launches")
     return n.value
+
+
+def retro_attend_plan(dims: Dims, selects: bool) -> Tuple[int, int]:
+    """(row tiles of a streamed attention workgroup or 0, splits) for dims on the
+    current device; selects: in a step of three launches."""
+    t, n = C.c_int32(0), C.c_int32(0)
+    _check(load_library().retro_attend_plan(C.byref(dims), 1 if selects else 0, C.byref(t),
+                                            C.byref(n)), "retro_attend_plan")
+    return t.value, n.value
 
 
 def retro_step_noalloc(dims: Dims, step: int, q_window, k_new, v_new, cache: KVCache,

@@ -361,6 +361,18 @@ bool select_in_attention(const Geometry& gp) {
 }
 }  // namespace
 
+retro_status retro_attend_plan(const retro_dims* dims, int32_t selects, int32_t* row_tiles,
+                               int32_t* splits) {
+  Geometry g;
+  if (!row_tiles || !splits) return RETRO_EINVAL;
+  retro_status st = prepare(dims, 0, &g);
+  if (st != RETRO_OK) return st;
+  const Geometry ga = retro::attend_geometry(g, selects != 0);
+  *row_tiles = ga.stream ? ga.tiles_per_group : 0;
+  *splits = ga.n_splits;
+  return RETRO_OK;
+}
+
 retro_status retro_step_launches(const retro_dims* dims, int32_t* launches) {
   Geometry g;
   if (!launches) return RETRO_EINVAL;

@@ -111,6 +111,8 @@ def test_null_pointers_and_small_workspace_rejected_before_any_launch(lib):
     assert raw.retro_prefill_kv(C.byref(d), C.byref(cache), 0, 2080 * 16 - 2, 4, 1, 1,
                                 None) == lib.RETRO_EINVAL
     assert raw.retro_k_max(None, C.byref(S())) == lib.RETRO_EINVAL
+    assert raw.retro_attend_plan(C.byref(d), 1, None, C.byref(S())) == lib.RETRO_EINVAL
+    assert raw.retro_attend_plan(None, 1, C.byref(S()), C.byref(S())) == lib.RETRO_EINVAL
 
 
 def test_project_f32_arguments_checked_on_the_host(lib):

@@ -200,7 +200,10 @@ def _proj_case(rows, K, nq, nkv, seed):
 @pytest.mark.parametrize("rows,K,nq,nkv", [(1, 1024, 256, 64), (5, 2048, 512, 128),
                                            (17, 4096, 4096, 1024), (34, 1024, 128, 32),
                                            (48, 3072, 64, 16), (20, 1024, 16, 16),
-                                           (72, 2048, 256, 64), (112, 1024, 64, 16)])
+                                           (72, 2048, 256, 64), (112, 1024, 64, 16),
+                                           # six and seven row tiles of whole shares
+                                           (96, 4096, 128, 32), (112, 4096, 128, 32),
+                                           (96, 2048, 128, 32), (112, 2048, 64, 16)])
 def test_project_qkv_matches_fp64_products(rows, K, nq, nkv):
     print(f"[proj] qkv rows={rows} K={K} nq={nq} nkv={nkv}", flush=True)
     got, ref, ref_b = _proj_case(rows, K, nq, nkv, seed=rows * 7 + K)
@@ -241,7 +244,10 @@ def test_projections_do_not_depend_on_the_number_of_columns(rows, K):
 
 
 @pytest.mark.parametrize("rows,K,n", [(1, 1024, 512), (17, 4096, 4096), (40, 2048, 256),
-                                      (18, 1024, 48), (72, 4096, 1024), (100, 1024, 256)])
+                                      (18, 1024, 48), (72, 4096, 1024), (100, 1024, 256),
+                                      (96, 4096, 256), (112, 4096, 256), (112, 2048, 64),
+                                      # more column tiles than compute units
+                                      (5, 2048, 4224), (20, 4096, 4224), (20, 2048, 4224)])
 def test_project_out_adds_the_residual(rows, K, n):
     import torch
     from paper_2508_09001_amd import binding as B

@@ -9,11 +9,21 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
-# batch, KV heads, G, W, dtype, flags: one split per KV head (256 heads of 16 rows; 64
-# heads of 36 rows in the bf16 attention launch), several, the one-launch step
-SHAPES = [(32, 8, 4, 3, "bf16", 1), (32, 8, 4, 3, "f32", 1), (8, 8, 4, 8, "bf16", 1),
+# batch, KV heads, G, W, dtype, flags: one split per KV head in the streamed attention
+# (256 heads of 1, 2, 3, 4 and 9 row tiles) and in the one through LDS (fp32), several
+# splits, the one-launch step
+STREAMED = [(32, 8, 4, 3, "bf16", 1), (32, 8, 4, 7, "bf16", 1), (32, 8, 4, 8, "bf16", 1),
+            (32, 8, 4, 15, "bf16", 1), (32, 8, 8, 16, "bf16", 1)]
+SHAPES = [*STREAMED, (32, 8, 4, 3, "f32", 1), (8, 8, 4, 8, "bf16", 1),
           (4, 8, 8, 32, "bf16", 1), (1, 2, 4, 3, "bf16", 1), (1, 2, 4, 3, "bf16", 0),
           (1, 2, 4, 3, "f32", 0), (1, 2, 4, 0, "bf16", 0)]
+
+
+def _streams(lay):
+    from paper_2508_09001_amd import binding as B
+    for selects in (False, True):
+        tiles, splits = B.retro_attend_plan(lay.dims, selects)
+        assert tiles > 0 and splits == 1
 
 
 def _run(shape, path, key):
@@ -24,6 +34,8 @@ def _run(shape, path, key):
     lay = RetroLayer(batch=b, num_kv_heads=hk, group=G, head_dim=d, page_size=P, budget=pages * P,
                      window=W, max_pages=pages, dtype=dtype, flags=flags)
     g = torch.Generator().manual_seed(W + hk)
+    if shape in STREAMED:
+        _streams(lay)
     keys = torch.randn(b * pages, hk, P, d, generator=g)
     if key is not None:
         keys.view(b, pages, hk, P, d)[:, 5, :, 3, 7] = key
@@ -67,7 +79,7 @@ def test_rows_that_use_a_nonfinite_key_are_nan(shape, path):
 # Scores far beyond the range in which a difference of two of them is exact in fp32:
 # the largest one's key takes the whole weight, and the log-normaliser is its score.
 @pytest.mark.parametrize("power", [4, 13, 18, 30])
-@pytest.mark.parametrize("shape", [(8, 8, 4, 8, "bf16", 1), (4, 8, 8, 32, "bf16", 1),
+@pytest.mark.parametrize("shape", [*STREAMED, (8, 8, 4, 8, "bf16", 1), (4, 8, 8, 32, "bf16", 1),
                                    (32, 8, 4, 3, "f32", 1), (1, 2, 4, 3, "bf16", 0)])
 def test_large_scores(shape, power):
     from paper_2508_09001_amd.layer import RetroLayer
@@ -76,6 +88,8 @@ def test_large_scores(shape, power):
     lay = RetroLayer(batch=b, num_kv_heads=hk, group=G, head_dim=d, page_size=P, budget=pages * P,
                      window=W, max_pages=pages, dtype=dtype, flags=flags)
     g = torch.Generator().manual_seed(W + hk + power)
+    if shape in STREAMED:
+        _streams(lay)
     lay.k_cache.copy_(torch.randn(b * pages, hk, P, d, generator=g) * 2.0 ** power)
     lay.v_cache.copy_(torch.randn(b * pages, hk, d, P, generator=g))
     lay.seq_lens.fill_(pages * P - 1)

@@ -1,8 +1,8 @@
 """GPU parity of the step's other launch sequences, on shapes whose default
 step runs scores, selection and attention in one launch, chosen through
 retro_dims.flags: the scores in a launch of their own with the selection in
-front of the attention (RETRO_FLAG_SEPARATE_SCORES), and the selection at the
-end of the score launch (RETRO_FLAG_SELECT_IN_SCORES).  Same bar as the other
+front of the attention (RETRO_FLAG_SEPARATE_SCORES), and the selection in a
+launch of its own after them (RETRO_FLAG_SELECT_IN_SCORES).  Same bar as the other
 parity tests: scores, selections, masks, A and sequence lengths bit for bit;
 outputs and log-normalisers within 2e-3 (bf16) and 1e-5 (fp32) max-abs."""
 import pytest
