@@ -23,18 +23,20 @@ namespace {
 // 19.0 us for 34 MB when every pass read the queries from LDS again, 13.1 us.
 constexpr int kScoreThreads = 512;
 constexpr int kScoreWaves = kScoreThreads / 64;
-constexpr int kScoreIters = 2;
-constexpr int kPassPages = kScoreWaves * 4;              // pages of a pass
-constexpr int kMaxPpb = kPassPages * kScoreIters;        // most pages a workgroup scores
+// A page of d 64 in bf16 is half as long: up to four passes (32 heads of 5386 pages
+// 10.7 -> 9.6 us).
+template <typename T, int D>
+constexpr int score_iters = D * sizeof(T) <= 128 ? 4 : 2;
+constexpr int kPassPages = kScoreWaves * 4;  // pages of a pass
 
 // Workgroups per KV head and pages per workgroup: two workgroups for every
-// compute unit while a pass each is left, at most kMaxPpb pages a workgroup.  With
+// compute unit while a pass each is left, at most `iters` passes a workgroup.  With
 // the selection at the end, one for every compute unit where that is enough, of
 // whole passes: 32 heads of 300 pages 8.7 us, 9.6 with two; 2 heads of 5900 pages
 // 13.8, in workgroups of 47 pages 14.2, of 24 15.7.
-void score_split(const Geometry& g, bool selects, int* nbh, int* ppb) {
+void score_split(const Geometry& g, int iters, bool selects, int* nbh, int* ppb) {
   const int heads = g.hk * g.batch, cus = compute_units();
-  const int n_min = (g.max_pages + kMaxPpb - 1) / kMaxPpb;
+  const int n_min = (g.max_pages + iters * kPassPages - 1) / (iters * kPassPages);
   const int n_max = (g.max_pages + kPassPages - 1) / kPassPages;
   int n = std::min(n_max, std::max(n_min, 2 * cus / heads));
   if (selects && (int64_t)n_max * heads > cus && (int64_t)n_min * heads <= cus) n = n_min;
@@ -88,7 +90,7 @@ __global__ void __launch_bounds__(kScoreThreads, PER ? 4 : 8) score_kernel(
     return tk;
   };
   float* srow = scores + bh * g.max_pages;
-  score_role<T, D, kScoreIters, false, 0, kScoreThreads>(
+  score_role<T, D, score_iters<T, D>, false, 0, kScoreThreads>(
       g, page0, page_end, q + b * q_bstride + (int64_t)h * g.G * D, dg + bh * g.max_pages * 2 * D,
       dyn_lds, tok_of, [] {},
       [&](int page, float v) {
@@ -123,8 +125,9 @@ hipError_t score_t(const Geometry& g, const void* q, int64_t qbs, const retro_kv
                    const void* k_new, const void* v_new, float* scores, const SelectArgs& sa,
                    hipStream_t s) {
   int nbh, ppb;
-  score_split(g, PER > 0, &nbh, &ppb);
-  if (ppb < 1 || ppb > kMaxPpb || nbh < 1) return hipErrorInvalidValue;
+  constexpr int IT = score_iters<T, D>;
+  score_split(g, IT, PER > 0, &nbh, &ppb);
+  if (ppb < 1 || ppb > IT * kPassPages || nbh < 1) return hipErrorInvalidValue;
   dim3 grid(nbh, g.hk, g.batch);
   size_t lds = sizeof(float) * 2 * g.G * D;  // the queries' q+ and q- halves
   if constexpr (PER > 0) lds = std::max(lds, sizeof(ThrLds<PER, kScoreWaves>));
