@@ -165,15 +165,16 @@ int compute_units() {
   return cus[dev];
 }
 
-// Up to here a call's host time, a launch fewer, is what the last workgroup's
-// selection saves at equal time on the GPU (128 heads of 250 pages 11.4 us both, 32
-// of 600 11.2 against 10.9 with a launch of its own, 2 of 4100 12.2 against 12.4);
-// past it the chain from a head's last score to its rows costs more (16 heads of
-// 2000 pages 13.7 against 13.1, 8 of 4090 16.7 against 15.0, 33K pages 16.0 against
-// 13.8, 131K 41 against 28).
+// Up to here a call's host time, a launch fewer (15 heads of 1870 pages, separate
+// calls of two layers 89 us a pass, 95 with it), is what the last workgroup's
+// selection saves at about equal time on the GPU (128 heads of 250 pages 11.4 us
+// both, 32 of 600 11.2 against 10.9 with a launch of its own, 16 of 2000 13.7
+// against 13.1, 2 of 4100 12.2 against 12.4); past it the chain from a head's last
+// score to its rows costs more (8 heads of 4090 pages 16.7 against 15.0, 33K pages
+// 16.0 against 13.8, 131K 41 against 28).
 bool score_selects(const Geometry& g) {
   const int64_t pages = (int64_t)g.batch * g.hk * g.max_pages;
-  return pages <= (g.max_pages <= 1024 ? 1 << 15 : 1 << 14) && g.max_pages <= kScoreThreads * kSelectPer;
+  return pages <= (g.max_pages <= 3072 ? 1 << 15 : 1 << 14) && g.max_pages <= kScoreThreads * kSelectPer;
 }
 
 hipError_t launch_score(const Geometry& g, const void* q_cur, int64_t q_batch_stride,
