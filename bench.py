@@ -16,7 +16,7 @@ replayed back to back in the timed region.
 Prints one JSON line with the throughput (effective HBM GB/s of the whole step,
 algorithmic bytes / time), microseconds per layer per step, the roofline of the
 dominant kernel (where retro_step is one launch, that launch: the whole step;
-else its scores + selection + attention launch, timed alone with HIP events),
+else its selection + attention launch, timed alone with HIP events),
 the gather phase alone (the attention kernel over the step's selection, timed
 with HIP events) and the CPU oracle's rate on a bounded sample.
 """
@@ -58,7 +58,7 @@ def _args():
     p.add_argument("--update-kv", action="store_true",
                    help="UpdateKV of the window's W past tokens before every step (Alg. 1)")
     p.add_argument("--attend-reps", type=int, default=4,
-                   help="scores + selection + attention launches per layer in the roofline measurement")
+                   help="selection + attention launches per layer in the roofline measurement")
     p.add_argument("--cpu-seconds", type=float, default=15.0,
                    help="budget of the CPU oracle sample (0 skips it)")
     p.add_argument("--decoder", type=int, default=0,
@@ -89,7 +89,8 @@ def _step_path(launches, reuse=0):
     if launches == 1:
         path = "one launch: scores, selection, attention, combine + merge"
     else:
-        path = (f"{launches} launches: scores (+ selection), [selection +] attention, "
+        path = (f"{launches} launches: scores, "
+                f"{'selection + attention' if launches == 3 else 'selection, attention'}, "
                 "combine + merge")
     if reuse >= 2:
         path = (f"refresh steps (t mod {reuse} == 0): {path}; other steps keep the selection: "
@@ -275,12 +276,11 @@ def main():
             if cnt.get("source_sha256") == _sha(STEP_SRC):
                 traffic = cnt.get("hbm_bytes_per_launch")
     else:
-        # the step's scores + selection + attention launch alone: digests ->
-        # scores -> selection -> gather, queries
-        kernel = "scores + selection + attention launch"
+        # the step's selection + attention launch alone (the digests are read by
+        # the score launch before it): scores -> selection -> gather, queries
+        kernel = "selection + attention launch"
         us_kernel = graph_us(lambda lay: lay.step_attend_partials(last, win_last))
-        kernel_bytes = (nbytes["digest"] + nbytes["gather"] + nbytes["queries"] +
-                        nbytes["select_reads"])
+        kernel_bytes = nbytes["gather"] + nbytes["queries"] + nbytes["select_reads"]
         n_kernel = n_att
     kernel_gbs = kernel_bytes / (us_kernel * 1e-6) / 1e9
     # the gather phase alone: the attention kernel over the step's selection
@@ -320,7 +320,9 @@ def main():
                      "frac": round(kernel_gbs / PEAK_HBM_GBS, 4), "traffic": traffic,
                      "bytes_per_launch": kernel_bytes, "us_per_launch": round(us_kernel, 3),
                      "launches": n_kernel},
-        "gather_phase": {"kernel": "attend_kernel (retro_decode_attend_partials)",
+        "gather_phase": {"kernel": ("stream_attend_kernel" if B.retro_attend_plan(
+                                        layers[0].dims, False)[0] else "attend_kernel") +
+                                   " (retro_decode_attend_partials)",
                          "bytes_per_launch": gather_bytes, "us_per_launch": round(us_gather, 3),
                          "achieved": round(gather_gbs, 1), "unit": "GB/s",
                          "frac": round(gather_gbs / PEAK_HBM_GBS, 4), "launches": n_att},

@@ -25,10 +25,11 @@
 //
 // Measured per launch, without the selection, attend_role's before: batch 16, 64
 // pages and 36 rows per KV head (67 MB) 28 -> 22 us; batch 8, 307 pages, 32 rows
-// (161 MB) 98 -> 38 us; 131K tokens dense, 68 rows (537 MB) 242 -> 125 us: bound
-// by HBM.  Batch 4, 256 pages, 264 rows (67 MB) 75 -> 55 us; 131K tokens, 256 pages
-// of 32, 260 rows (34 MB) 45 -> 27 us: bound by vector instructions (38 % of the
-// cycles the matrix cores are busy, 54 % the vector units).
+// (161 MB) 98 -> 38 us; 131K tokens dense, 68 rows (537 MB) 242 -> 110 us: bound
+// by HBM, 4.9 TB/s.  Batch 4, 256 pages, 264 rows (67 MB) 75 -> 46 us; 131K tokens,
+// 256 pages of 32, 260 rows (34 MB) 45 -> 25 us: bound by vector instructions (38 %
+// of the cycles the matrix cores are busy, 54 % the vector units).  (The pairs of
+// figures at single choices, here and below, were taken when each was made.)
 #include <algorithm>
 
 #include "threshold.h"
