@@ -2,6 +2,7 @@
 and rejects bad arguments on the host before anything is enqueued."""
 import ctypes as C
 import os
+import random
 import re
 
 import pytest
@@ -135,3 +136,30 @@ def test_append_tokens_arguments_checked_on_the_host(lib):
     assert raw.retro_append_kv_tokens(C.byref(d), 0, C.byref(bad), 2, 1, 1, None) == lib.RETRO_EINVAL
     # no tokens: nothing to do, no launch
     assert raw.retro_append_kv_tokens(C.byref(d), 0, C.byref(cache), 0, None, None, None) == lib.RETRO_OK
+
+
+def test_split_partials_of_every_attention_plan_fit_the_workspace(lib):
+    """The attention launches choose their own splits; the workspace is sized for
+    the largest of them (and the counts cover the selection)."""
+    rng = random.Random(5)
+    streamed = 0
+    for _ in range(3000):
+        P = rng.choice([16, 32])
+        mp = int(2 ** rng.uniform(0, 14))
+        kw = dict(batch=rng.choice([1, 2, 5, 16, 64, 300]), num_kv_heads=rng.choice([1, 2, 5, 8, 32]),
+                  group=rng.choice([1, 3, 4, 8, 16]), head_dim=rng.choice([64, 128]), page_size=P,
+                  budget_tokens=P * int(2 ** rng.uniform(0, 14)), window=rng.choice([0, 1, 4, 15, 16, 63]),
+                  max_pages=mp, num_phys_pages=mp)
+        d = _dims(lib, **kw)
+        try:
+            ws = lib.retro_workspace_size(d)
+        except lib.RetroError:
+            continue
+        rows = d.batch * d.num_kv_heads * (d.window + 1) * d.group
+        fixed = d.batch * d.num_kv_heads * (4 * mp + 4 * lib.retro_k_max(d))
+        for selects in (False, True):
+            tiles, splits = lib.retro_attend_plan(d, selects)
+            streamed += tiles > 0
+            assert 0 <= tiles <= 6 and 1 <= splits <= lib.retro_k_max(d)
+            assert fixed + splits * rows * (d.head_dim + 1) * 4 <= ws, kw
+    assert streamed > 500
